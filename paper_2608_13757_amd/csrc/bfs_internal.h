@@ -64,19 +64,31 @@ inline bool pack_wait(const DevWait &d, PackedWait &out) {
   return true;
 }
 
+// The interpreter's tables, each engine's part contiguous:
+//   code         4 x int32 per word: {kind | ..., ...}, by kind
+//                LOOP {1, loop, its END word, parent}, END {2, loop, its LOOP
+//                word, 0}, TRACK {5, producer engine, instructions passed, 0},
+//                SNAP {6 | producer engine << 8 | loop S << 16, snapshots
+//                kept, first snapshot word, 0}, INSTR {3 | opcode << 8 |
+//                innermost loop << 16 | (counter slot + 1) << 24, instruction
+//                row, first wait row, waits}; rows and words count from the
+//                engine's first
+//   engine_off   [3][n_engines + 1]: each engine's first code word,
+//                instruction row and wait row
+//   instr_args   8 x int32 per instruction: its args
+//   waits        8 x int32 per wait: {counter | loop P << 8 | loop S << 16 |
+//                mask << 24 | linearized << 25, dependency, k, v, N, K,
+//                snapshots kept, 0} with v the barrier-mode ordinal, the first
+//                snapshot word (per-engine) or expr_sub
 struct DevImage {
   int device = -1;
   void *mem = nullptr;          // one allocation holding everything below
-  int32_t *code = nullptr;      // int32 x4 per word
-  int32_t *code_off = nullptr;  // [n_engines + 1] in words
-  DevWait *waits = nullptr;
-  int32_t *instr_opcode = nullptr;
+  int32_t *code = nullptr;
+  int32_t *engine_off = nullptr;
   int32_t *instr_args = nullptr;
-  int32_t *instr_waits = nullptr;  // CSR [n_instrs + 1] into waits_by_instr
-  int32_t *waits_by_instr = nullptr;
-  int32_t *instr_update = nullptr; // counter slot each instruction increments, -1 none
-  int32_t *loop_parent = nullptr;
-  uint32_t *err = nullptr;         // watchdog word: [code, dep, wg, instance, thr, observed, wave, pad]
+  int32_t *waits = nullptr;
+  int32_t n_waits[kMaxEngines] = {};   // wait rows of each engine
+  uint32_t *err = nullptr;      // error words: [code, dep, wg, instance, thr, observed, wave, pad]
 };
 
 bfs_status launch_gemm(const bfs_plan *p, DevImage *img, const void *const *bufs, int32_t nbufs,
@@ -128,6 +140,7 @@ struct bfs_plan {
   // and the devices whose static array this plan has written (bit d).
   std::vector<unsigned char> packed;
   std::vector<size_t> packed_off;        // table offsets in `packed`
+  int32_t packed_waits[bfs::kMaxEngines] = {};   // wait rows of each engine
   uint64_t uid = 0;
   uint64_t noalloc_devices = 0;
 };

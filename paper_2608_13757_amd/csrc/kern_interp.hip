@@ -10,6 +10,27 @@
 // Opcodes (see the program description): 0 no-op, 1 load tile into a ring
 // slot, 2 acc += c * slot, 3 store acc to output tile wg, 4 slot + c into a
 // second ring, 5 store a slot to output tile gidx.
+//
+// What bounds it: the chain of dependent accesses behind each instruction
+// (code word, descriptors, loop registers, counter poll) and the memory
+// latency of its load.  So:
+//   * the engine's program and the loop registers live in vector registers,
+//     one code word, descriptor or loop per lane, read with v_readlane (a few
+//     clocks) instead of from memory or LDS.  That takes at most 64 code words
+//     and 64 waits per engine; longer programs read the same tables with
+//     scalar loads (kLanes false).
+//   * loads go directly to LDS and stay in flight, up to 8 tiles, with
+//     stores counted in the same queue; they retire in issue order with
+//     counted vmcnt waits: the oldest when the queue is full, one at a time
+//     while the engine is blocked on a wait (its consumers may be waiting for
+//     exactly those), all of them before any other instruction retires and at
+//     every barrier.  Instrumented launches retire each instruction at once.
+//   * a wait already met by the last observed counter value (counters only
+//     grow, barrier mode aside) is not polled again.
+// The ring program (64 outer iterations, 4 slots, 1024 workgroups, 303 MB of
+// tiles) takes 496 us against 1705 us with tables, loop registers and
+// execution counts read from memory and LDS and every instruction drained
+// before the next.
 #include "bfs_internal.h"
 #include "device_sync.h"
 
@@ -18,17 +39,15 @@ using namespace bfsdev;
 namespace {
 
 constexpr int kMaxInstrsInterp = 256;
+constexpr uint32_t kMaxPending = 8;     // vector-memory instructions in flight per engine
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct InterpParams {
-  const int32_t *code;          // int32 x4 words
-  const int32_t *code_off;      // [n_engines + 1]
-  const bfs::DevWait *waits;    // [n_deps]
-  const int32_t *instr_waits;   // CSR [n_instrs + 1]
-  const int32_t *waits_by_instr;
-  const int32_t *instr_opcode;
-  const int32_t *instr_args;    // [n_instrs][8]
-  const int32_t *instr_update;  // counter slot or -1
-  const int32_t *loop_parent;
+  const int32_t *code;          // code words, 4 x int32
+  const int32_t *engine_off;    // [3][n_engines + 1]: first code word, instruction row, wait row
+  const int32_t *waits;         // wait rows, 8 x int32
+  const int32_t *args;          // instruction rows: args[8]
   const int32_t *trips;
   const int64_t *trip_off;
   const int64_t *base;
@@ -40,203 +59,374 @@ struct InterpParams {
   uint64_t *stats;              // per-wave statistics (null: off)
   uint64_t watchdog;
   int32_t fault_dep, fault_delta;
-  int32_t n_loops, n_engines, n_instrs, mode, tile;
+  int32_t n_loops, n_engines, tile;
+  int32_t wide_x, wide_out;     // tiles of 256 in a 16-byte aligned buffer: one 16-byte access per lane
   uint32_t fallback_loops;      // bit l: drain barrier at the end of every iteration of loop l
   int32_t ring_off[4];          // float offsets in the ring area
   int32_t acc_off;
-  int32_t lds_state_off, lds_exec_off, lds_data_off;   // byte offsets in dynamic LDS
+  int32_t data_floats;
+  int32_t lds_data_off;         // byte offset in dynamic LDS
   int32_t lds_snap_off, snap_words;   // per-engine allocation: running counts and snapshots per wave
 };
 
-__device__ __forceinline__ int slot_of(const int32_t *a, const uint32_t *r, const uint32_t *rhat) {
-  int hi = 0;
-  if (a[2] >= 0) hi = (int)((r[a[2]] - 1u) % (uint32_t)a[3]) * a[5];
-  int lo = (a[4] >= 0) ? (int)((rhat[a[4]] - 1u) % (uint32_t)a[5]) : 0;
-  return hi + lo;
+__device__ __forceinline__ uint32_t rl(uint32_t v, uint32_t lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane);
 }
 
+// v with lane l replaced by x (l and x wave-uniform)
+__device__ __forceinline__ uint32_t wl(uint32_t v, uint32_t l, uint32_t x) { return lane_id() == l ? x : v; }
+
+// a % b; ring depths are small and often powers of two
+__device__ __forceinline__ uint32_t umod(uint32_t a, uint32_t b) {
+  if ((b & (b - 1u)) == 0u) return a & (b - 1u);
+  return a < b ? a : a % b;
+}
+
+// At most n <= 15 vector-memory instructions outstanding (fewer for the counts
+// that no queue of kMaxPending equal entries leaves).
+__device__ __forceinline__ void wait_at_most(uint32_t n) {
+  n = uniform(n);
+  if (n < 4u) {
+    if (n < 2u) {
+      if (n == 0u) wait_vm<0>(); else wait_vm<1>();
+    } else {
+      if (n == 2u) wait_vm<2>(); else wait_vm<3>();
+    }
+  } else if (n < 8u) {
+    if (n < 6u) {
+      if (n == 4u) wait_vm<4>(); else wait_vm<5>();
+    } else {
+      if (n == 6u) wait_vm<6>(); else wait_vm<7>();
+    }
+  } else {
+    if (n < 12u) wait_vm<8>(); else wait_vm<12>();
+  }
+}
+
+// kLanes: the engine's code words, instruction rows and wait rows each fit
+// the 64 lanes of a register (the launcher checks); otherwise they are read
+// with scalar loads.
+template <int kMode, bool kInstr, bool kLanes>
 __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   uint32_t *cnt = reinterpret_cast<uint32_t *>(lds);            // [64 slots][8 waves]
   const int wave = wave_id();
   const uint32_t lane = lane_id();
   const int wg = blockIdx.x;
-  uint32_t *st = reinterpret_cast<uint32_t *>(lds + P.lds_state_off) + wave * 3 * bfs::kMaxLoops;
-  uint32_t *r = st, *rhat = st + bfs::kMaxLoops, *trip = st + 2 * bfs::kMaxLoops;
-  uint32_t *execn = reinterpret_cast<uint32_t *>(lds + P.lds_exec_off) + wave * kMaxInstrsInterp;
+  const uint32_t e = (uint32_t)wave, E1 = (uint32_t)P.n_engines + 1u;
   float *data = reinterpret_cast<float *>(lds + P.lds_data_off);
+
+  // The engine's program: lane i holds code word i, instruction row i and
+  // wait row i.  (Loaded before the zeroing below so that the latencies
+  // overlap.)
+  const uint32_t code0 = (uint32_t)ldc(P.engine_off + e), code1 = (uint32_t)ldc(P.engine_off + e + 1);
+  const uint32_t row0 = (uint32_t)ldc(P.engine_off + E1 + e), row1 = (uint32_t)ldc(P.engine_off + E1 + e + 1);
+  const uint32_t wait0 = (uint32_t)ldc(P.engine_off + 2 * E1 + e), wait1 = (uint32_t)ldc(P.engine_off + 2 * E1 + e + 1);
+  uint32_t cw[4] = {}, ar[8] = {}, wr[8] = {};
+  if (kLanes) {
+    if (lane < code1 - code0)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) cw[j] = (uint32_t)P.code[4 * (code0 + lane) + j];
+    if (lane < row1 - row0)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) ar[j] = (uint32_t)P.args[8 * (row0 + lane) + j];
+    if (lane < wait1 - wait0)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) wr[j] = (uint32_t)P.waits[8 * (wait0 + lane) + j];
+  }
+  auto code = [&](uint32_t pc, int j) { return kLanes ? rl(cw[j], pc) : (uint32_t)ldc(P.code + 4 * (code0 + pc) + j); };
+  auto arg = [&](uint32_t row, int j) { return kLanes ? rl(ar[j], row) : (uint32_t)ldc(P.args + 8 * (row0 + row) + j); };
+  auto wrow = [&](uint32_t w, int j) { return kLanes ? rl(wr[j], w) : (uint32_t)ldc(P.waits + 8 * (wait0 + w) + j); };
+  // Loop registers and trip-table offsets, loop l in lane l (at most 32).
+  uint32_t rv = lane == 0 ? 1u : 0u, hv = rv, tv = rv;
+  uint32_t off_lo = 0, off_hi = 0;
+  if (lane < (uint32_t)P.n_loops) {
+    const int64_t o = P.trip_off[(int64_t)wg * P.n_loops + lane];
+    off_lo = (uint32_t)o;
+    off_hi = (uint32_t)((uint64_t)o >> 32);
+  }
+  const int64_t tbase = P.base ? ldc(P.base + wg) : 0;   // programs without loads and stores need none
+
+  // Zero counters, snapshots and data (rings and accumulators).
+  for (int i = threadIdx.x; i < bfs::kMaxSlots * bfs::kMaxWavesPerEngine; i += blockDim.x) cnt[i] = 0;
   // per-engine allocation: words 0 .. kMaxEngines - 1 hold the running count
   // of each producer engine's instructions up to this wave's position, then
   // the dependencies' snapshots
-  uint32_t *snap = reinterpret_cast<uint32_t *>(lds + P.lds_snap_off) + wave * P.snap_words;
-
-  // Zero counters, state and accumulators.
-  for (int i = threadIdx.x; i < bfs::kMaxSlots * bfs::kMaxWavesPerEngine; i += blockDim.x) cnt[i] = 0;
-  for (int i = lane; i < 3 * bfs::kMaxLoops; i += 64) st[i] = 0;
-  for (int i = lane; i < P.n_instrs; i += 64) execn[i] = 0;
-  for (int i = lane; i < P.snap_words; i += 64) snap[i] = 0;
-  for (int i = threadIdx.x; i < (P.acc_off + 4 * P.tile); i += blockDim.x) data[i] = 0.f;
+  uint32_t *snap_p = reinterpret_cast<uint32_t *>(lds + P.lds_snap_off) + wave * P.snap_words;
+  for (int i = lane; i < P.snap_words; i += 64) snap_p[i] = 0;
+  for (int i = threadIdx.x; i < P.data_floats; i += blockDim.x) data[i] = 0.f;
   __syncthreads();
+  // The program has arrived: taken here, so that the compiler does not place
+  // a wait for these loads (which would wait for every load in flight) at
+  // their uses in the loop.
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j < 4) asm volatile("" : "+v"(cw[j]));
+    asm volatile("" : "+v"(ar[j]), "+v"(wr[j]));
+  }
+  asm volatile("" : "+v"(off_lo), "+v"(off_hi));
 
-  const int e = wave;
-  const uint32_t cnt_base = lds_addr(cnt);
-  const uint32_t own_words = cnt_base + 4u * (uint32_t)(e * bfs::kMaxWavesPerEngine);
+  const uint32_t snap = lds_addr(snap_p);
+  const uint32_t cnt_base = lds_addr(cnt), data_l = lds_addr(data);
+  auto counter = [&](uint32_t slot) { return cnt_base + 4u * slot * (uint32_t)bfs::kMaxWavesPerEngine; };
+  const uint32_t own_words = counter(e);
   uint32_t *log_entries = nullptr;
   uint32_t nlog = 0;
-  if (P.dbg) {
+  if (kInstr && P.dbg) {
     const int64_t nw = (int64_t)gridDim.x * P.n_engines;
     log_entries = P.dbg + nw + ((int64_t)wg * P.n_engines + wave) * 4 * P.dbg_cap;
   }
-  bool aborted = false;
   WaveStats stt;
-  if (P.stats) {
+  if (kInstr && P.stats) {
     stt.on = true;
     stt.t_start = now_ticks();
   }
-  if (lane == 0) { r[0] = 1; rhat[0] = 1; trip[0] = 1; }
-  __builtin_amdgcn_s_waitcnt(0);
+  const uint32_t limit = P.watchdog > 0xffffffffull ? 0xffffffffu : (uint32_t)P.watchdog;
+  const uint32_t T = (uint32_t)P.tile;
+  const uint32_t ld_ops = P.wide_x ? 1u : T / 64u, st_ops = P.wide_out ? 1u : T / 64u;   // accesses per tile
+  uint32_t aborted = 0;
+  uint32_t seen = 0;                       // lane w: last observed counter value of wait w (w < 64)
 
-  const int32_t *code = P.code + 4 * P.code_off[e];
-  int pc = 0;
-  const int64_t *toff = P.trip_off + (int64_t)wg * P.n_loops;
+  // Issued, unretired loads and stores, oldest first: counter slot + 1 (0
+  // none) in 8 bits each.  All entries of the queue have the same number of
+  // vector-memory instructions (ops), which the counted waits rely on: a
+  // change of it empties the queue first.
+  uint64_t queue = 0;
+  uint32_t pending = 0, ops = 1;
+  auto add_slot = [&](uint32_t slot1) {
+    if (slot1 != 0u) lds_add(counter(slot1 - 1u), 1u);
+  };
+  auto retire_one = [&]() {
+    pending -= 1;
+    wait_at_most(pending * ops);
+    add_slot((uint32_t)queue & 0xffu);
+    queue >>= 8;
+  };
+  auto retire_all = [&]() {
+    if (pending > 0) {
+      wait_vm<0>();
+      for (; pending > 0; --pending, queue >>= 8) add_slot((uint32_t)queue & 0xffu);
+    }
+  };
+  auto issued = [&](uint32_t slot1) {      // one more instruction of `ops` accesses is in flight
+    queue |= (uint64_t)slot1 << (8u * pending);
+    pending += 1;
+    if (kInstr) retire_all();
+    else if (pending == kMaxPending || (pending + 1u) * ops > 16u) retire_one();
+  };
+  auto want_ops = [&](uint32_t n) {
+    if (ops != n) {
+      retire_all();
+      ops = n;
+    }
+  };
+  auto barrier_point = [&]() {             // Section 3.4: drain, meet, reset, meet
+    retire_all();
+    const uint64_t t0 = (kInstr && stt.on) ? now_ticks() : 0;
+    region_sync(own_words, 1);
+    if (kInstr && stt.on) stt.barrier += now_ticks() - t0;
+    seen = 0;                              // the counters were reset
+  };
+  // Poll until the counter reaches thr, retiring what this engine holds.
+  auto poll_until = [&](uint32_t addr, uint32_t thr, uint32_t dep, uint32_t inst) -> uint32_t {
+    uint32_t polls = 0;
+    while (true) {
+      const uint32_t v = uniform(lds_poll(addr));
+      if (v >= thr) return v;
+      if (pending > 0) {
+        retire_one();
+        continue;
+      }
+      if (++polls > limit) {
+        report_deadlock(P.err, dep, (uint32_t)wg, inst, thr, v, (uint32_t)wave);
+        aborted = 1u;
+        return v;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  };
+
+  uint32_t pc = 0;
   while (true) {
-    const int kind = code[4 * pc], a0 = code[4 * pc + 1], a1 = code[4 * pc + 2];
-    if (kind == bfs::CODE_HALT) break;
-    if (kind == bfs::CODE_LOOP) {
-      if (P.mode == BFS_MODE_BARRIER) {
-        const uint64_t t0 = stt.on ? now_ticks() : 0;
-        region_sync(own_words, 1);
-        if (stt.on) stt.barrier += now_ticks() - t0;
+    const uint32_t w0 = code(pc, 0), kind = w0 & 0xffu;
+    const uint32_t w1 = code(pc, 1), w2 = code(pc, 2), w3 = code(pc, 3);
+    if (__builtin_expect(kind == bfs::CODE_INSTR, 1)) {
+      // CODE_INSTR: w0 = kind | opcode << 8 | innermost loop << 16 | (counter
+      // slot + 1) << 24, w1 its row, w2 its first wait row, w3 its waits.  The
+      // innermost loop runs it once per iteration: r counts its executions.
+      const uint32_t op = (w0 >> 8) & 0xffu, n_waits = w3, slot1 = w0 >> 24;
+      const uint32_t inst = rl(rv, (w0 >> 16) & 0xffu) - 1u;
+      for (uint32_t w = w2; w < w2 + n_waits; ++w) {
+        const uint32_t q0 = wrow(w, 0), dep = wrow(w, 1);
+        const uint32_t mask = (q0 >> 24) & 1u, linear = (q0 >> 25) & 1u;
+        uint32_t thr;
+        if (kMode == BFS_MODE_BARRIER) {
+          thr = wrow(w, 3);
+        } else {
+          const uint32_t k = wrow(w, 2), q3 = wrow(w, 3), slots = wrow(w, 6);
+          const uint32_t lS = (q0 >> 16) & 0xffu, hS = rl(hv, lS);
+          if (slots > 0u) {
+            // per-engine: the snapshot of iteration r_S - k (or the latest
+            // one), under the mask of Eq. 5
+            const uint32_t rS = rl(rv, lS);
+            const bool owed = linear ? rS > k : (!mask || hS > k);
+            const uint32_t idx = slots > 1u ? umod(rS - k, slots) : 0u;
+            thr = owed ? uniform(lds_poll(snap + 4u * (q3 + idx))) : 0u;
+          } else {
+            thr = eq5(rl(rv, (q0 >> 8) & 0xffu), hS, (int)k, (int)q3, (int)wrow(w, 4), (int)wrow(w, 5), (int)mask);
+          }
+        }
+        if (kInstr && (int)dep == P.fault_dep) thr += (uint32_t)P.fault_delta;
+        uint32_t obs = 0;
+        if (!aborted && thr > 0u && (kInstr || w >= 64u || thr > rl(seen, w & 63u))) {
+          const uint64_t t0 = (kInstr && stt.on) ? now_ticks() : 0;
+          obs = poll_until(counter(q0 & 0xffu), thr, dep, inst);
+          if (w < 64u) seen = wl(seen, w, obs);
+          if (kInstr && stt.on) {
+            stt.blocked += now_ticks() - t0;
+            stt.n_blocked += 1;
+          }
+        }
+        if (kInstr) log_wait(log_entries, P.dbg_cap, nlog, dep, inst, thr, obs);
       }
-      const int l = a0;
-      const uint32_t rp = uniform(r[P.loop_parent[l]]);
-      const uint32_t t = (uint32_t)P.trips[toff[l] + (int64_t)rp - 1];
-      if (lane == 0) { rhat[l] = 0; trip[l] = t; }
-      if (t == 0) {
-        pc = a1 + 1;
+      // Datapath.
+      bool in_flight = false;                // retires later, in order
+      if (!aborted && op != 0u) {
+        // ring slot and tile index
+        auto slot_of = [&]() {
+          const int32_t a2 = (int32_t)arg(w1, 2), a4 = (int32_t)arg(w1, 4);
+          uint32_t s = a4 >= 0 ? umod(rl(hv, (uint32_t)a4) - 1u, arg(w1, 5)) : 0u;
+          if (a2 >= 0) s += umod(rl(rv, (uint32_t)a2) - 1u, arg(w1, 3)) * arg(w1, 5);
+          return s;
+        };
+        auto ring_at = [&](uint32_t id) {    // 0 .. 3, selected without indexing (stays in scalar registers)
+          return (uint32_t)(id == 0 ? P.ring_off[0] : id == 1 ? P.ring_off[1] : id == 2 ? P.ring_off[2] : P.ring_off[3]);
+        };
+        auto tile_of = [&]() { return (tbase + (int64_t)rl(rv, arg(w1, 6)) - 1) * (int64_t)T; };
+        // writes the registers of one tile to HBM as st_ops stores, in flight
+        auto store_tile = [&](uint32_t src, float *dst) {
+          want_ops(st_ops);
+          if (P.wide_out) {
+            *reinterpret_cast<f32x4 *>(dst + 4 * lane) = *(const BFS_LDS f32x4 *)(uintptr_t)(src + 16u * lane);
+          } else {
+            for (uint32_t i = 0; i < T; i += 64u) dst[i + lane] = *(const BFS_LDS float *)(uintptr_t)(src + 4u * (i + lane));
+          }
+          in_flight = true;
+        };
+        if (op == 1u) {          // load
+          want_ops(ld_ops);
+          const float *src = P.x + tile_of();
+          const uint32_t dst = data_l + 4u * (ring_at(arg(w1, 1)) + slot_of() * T);
+          if (P.wide_x) {
+            __builtin_amdgcn_global_load_lds((const void *)(src + 4 * lane), (BFS_LDS void *)(uintptr_t)dst, 16, 0, 0);
+          } else {
+            for (uint32_t i = 0; i < T; i += 64u)
+              __builtin_amdgcn_global_load_lds((const void *)(src + i + lane), (BFS_LDS void *)(uintptr_t)(dst + 4u * i), 4, 0, 0);
+          }
+          in_flight = true;
+        } else {
+          // the engine's earlier loads have landed before it reads a slot, and
+          // retire before this instruction does
+          retire_all();
+          const float c = __uint_as_float(arg(w1, 7));
+          if (op == 2u) {        // acc += c * slot
+            const uint32_t src = data_l + 4u * (ring_at(arg(w1, 0)) + slot_of() * T);
+            const uint32_t acc = data_l + 4u * ((uint32_t)P.acc_off + arg(w1, 1) * T);
+            if (T == 256u) {
+              BFS_LDS f32x4 *a = (BFS_LDS f32x4 *)(uintptr_t)(acc + 16u * lane);
+              f32x4 v = *a;
+              const f32x4 s = *(const BFS_LDS f32x4 *)(uintptr_t)(src + 16u * lane);
+  #pragma unroll
+              for (int j = 0; j < 4; ++j) v[j] = v[j] + c * s[j];
+              *a = v;
+            } else {
+              for (uint32_t i = lane; i < T; i += 64u) {
+                BFS_LDS float *a = (BFS_LDS float *)(uintptr_t)(acc + 4u * i);
+                *a = *a + c * *(const BFS_LDS float *)(uintptr_t)(src + 4u * i);
+              }
+            }
+          } else if (op == 3u) { // store acc
+            store_tile(data_l + 4u * ((uint32_t)P.acc_off + arg(w1, 0) * T), P.out + (int64_t)wg * T);
+          } else if (op == 4u) { // slot + c
+            const uint32_t s = slot_of() * T;
+            const uint32_t src = data_l + 4u * (ring_at(arg(w1, 0)) + s), dst = data_l + 4u * (ring_at(arg(w1, 1)) + s);
+            for (uint32_t i = lane; i < T; i += 64u)
+              *(BFS_LDS float *)(uintptr_t)(dst + 4u * i) = *(const BFS_LDS float *)(uintptr_t)(src + 4u * i) + c;
+          } else if (op == 5u) { // store slot
+            store_tile(data_l + 4u * (ring_at(arg(w1, 0)) + slot_of() * T), P.out + tile_of());
+          }
+        }
+      }
+      // Retire in program order.  LDS executes a wave's operations in issue
+      // order, so the add lands after the instruction's LDS reads and writes.
+      if (in_flight) {
+        issued(slot1);
       } else {
-        if (lane == 0) { r[l] += 1; rhat[l] = 1; }
-        pc += 1;
+        retire_all();
+        add_slot(slot1);
       }
-      __builtin_amdgcn_s_waitcnt(0);
+      pc += 1;
       continue;
     }
-    if (kind == bfs::CODE_END) {
-      const int l = a0;
-      if (P.mode == BFS_MODE_BARRIER) {
-        const uint64_t t0 = stt.on ? now_ticks() : 0;
-        region_sync(own_words, 1);
-        if (stt.on) stt.barrier += now_ticks() - t0;
+    if (kind == bfs::CODE_END) {           // w1 loop, w2 its loop word
+      const uint32_t l = w1;
+      if (kMode == BFS_MODE_BARRIER) {
+        barrier_point();
       } else if ((P.fallback_loops >> l) & 1u) {
         // Section 5.2 fallback: everything issued in this iteration of l has
         // retired on every engine before any engine starts the next one.
         // Every engine walks the same loop tree with the same trip table, so
         // all waves meet the same sequence of barriers.
+        retire_all();
         drain_all();
         __builtin_amdgcn_s_barrier();
       }
-      if (uniform(rhat[l]) < uniform(trip[l])) {
-        if (lane == 0) { r[l] += 1; rhat[l] += 1; }
-        pc = a1 + 1;
+      const uint32_t h = rl(hv, l);
+      if (h < rl(tv, l)) {
+        rv = wl(rv, l, rl(rv, l) + 1u);
+        hv = wl(hv, l, h + 1u);
+        pc = w2 + 1;
       } else {
         pc += 1;
       }
-      __builtin_amdgcn_s_waitcnt(0);
       continue;
     }
-    if (kind == bfs::CODE_TRACK) {
-      if (lane == 0) snap[a0] += (uint32_t)a1;
-      __builtin_amdgcn_s_waitcnt(0);
-      pc += 1;
-      continue;
-    }
-    if (kind == bfs::CODE_SNAP) {
-      // the producer engine's running count right after the producer's
-      // position, kept for the iteration of S it belongs to
-      const bfs::DevWait W = P.waits[a0];
-      const uint32_t slots = (uint32_t)W.snap_slots;
-      const uint32_t idx = slots > 1 ? uniform(r[W.loop_S]) % slots : 0u;
-      const uint32_t v = uniform(snap[W.prd_engine]);
-      if (lane == 0) snap[W.snap_off + idx] = v;
-      __builtin_amdgcn_s_waitcnt(0);
-      pc += 1;
-      continue;
-    }
-    // CODE_INSTR
-    const int ins = a0;
-    const uint32_t inst = uniform(execn[ins]);
-    for (int wi = P.instr_waits[ins]; wi < P.instr_waits[ins + 1]; ++wi) {
-      const bfs::DevWait W = P.waits[P.waits_by_instr[wi]];
-      uint32_t thr;
-      if (P.mode == BFS_MODE_BARRIER) {
-        thr = W.active ? (uint32_t)W.ordinal : 0u;
-      } else if (W.snap_slots > 0) {
-        // per-engine: the snapshot of iteration r_S - k (or the latest one),
-        // under the mask of Eq. 5
-        const uint32_t slots = (uint32_t)W.snap_slots, k = (uint32_t)W.k;
-        const uint32_t rS = uniform(r[W.loop_S]), hS = uniform(rhat[W.loop_S]);
-        const bool owed = W.linear ? rS > k : (!W.needs_mask || hS > k);
-        const uint32_t idx = slots > 1 ? (rS - k) % slots : 0u;
-        thr = owed ? uniform(snap[W.snap_off + idx]) : 0u;
+    if (kind == bfs::CODE_LOOP) {          // w1 loop, w2 its end word, w3 parent
+      if (kMode == BFS_MODE_BARRIER) barrier_point();
+      const uint32_t l = w1, rp = rl(rv, w3);
+      const int64_t o = (int64_t)((uint64_t)rl(off_lo, l) | (uint64_t)rl(off_hi, l) << 32);
+      const uint32_t t = (uint32_t)ldc(P.trips + o + (int64_t)rp - 1);
+      tv = wl(tv, l, t);
+      if (t == 0) {
+        hv = wl(hv, l, 0u);
+        pc = w2 + 1;
       } else {
-        thr = eq5(uniform(r[W.loop_P]), uniform(rhat[W.loop_S]), W.k, W.expr_sub, W.N, W.K, W.needs_mask);
+        rv = wl(rv, l, rl(rv, l) + 1u);
+        hv = wl(hv, l, 1u);
+        pc += 1;
       }
-      if (W.dep == P.fault_dep) thr += (uint32_t)P.fault_delta;
-      WaitResult res{0, true};
-      if (!aborted) {
-        const uint32_t addr = cnt_base + 4u * (uint32_t)(W.counter * bfs::kMaxWavesPerEngine);
-        const uint64_t t0 = stt.on ? now_ticks() : 0;
-        res = wait_geq(addr, 1, thr, P.watchdog);
-        if (stt.on && thr > 0) {
-          const uint64_t dt = now_ticks() - t0;
-          stt.blocked += dt;
-          stt.n_blocked += 1;
-        }
-        if (!res.ok) {
-          report_deadlock(P.err, (uint32_t)W.dep, (uint32_t)wg, inst, thr, res.observed, (uint32_t)wave);
-          aborted = true;
-        }
-      }
-      log_wait(log_entries, P.dbg_cap, nlog, (uint32_t)W.dep, inst, thr, res.observed);
+      continue;
     }
-    // Datapath.
-    if (!aborted) {
-      const int32_t *a = P.instr_args + 8 * ins;
-      const int op = P.instr_opcode[ins];
-      const int T = P.tile;
-      const float c = __int_as_float(a[7]);
-      if (op == 1) {          // load
-        const int64_t g = P.base[wg] + (int64_t)r[a[6]] - 1;
-        float *dst = data + P.ring_off[a[1]] + slot_of(a, r, rhat) * T;
-        for (int i = lane; i < T; i += 64) dst[i] = P.x[g * T + i];
-      } else if (op == 2) {   // acc += c * slot
-        const float *src = data + P.ring_off[a[0]] + slot_of(a, r, rhat) * T;
-        float *acc = data + P.acc_off + a[1] * T;
-        for (int i = lane; i < T; i += 64) acc[i] = acc[i] + c * src[i];
-      } else if (op == 3) {   // store acc
-        const float *acc = data + P.acc_off + a[0] * T;
-        for (int i = lane; i < T; i += 64) P.out[(int64_t)wg * T + i] = acc[i];
-      } else if (op == 4) {   // slot + c
-        const int s = slot_of(a, r, rhat);
-        const float *src = data + P.ring_off[a[0]] + s * T;
-        float *dst = data + P.ring_off[a[1]] + s * T;
-        for (int i = lane; i < T; i += 64) dst[i] = src[i] + c;
-      } else if (op == 5) {   // store slot
-        const int64_t g = P.base[wg] + (int64_t)r[a[6]] - 1;
-        const float *src = data + P.ring_off[a[0]] + slot_of(a, r, rhat) * T;
-        for (int i = lane; i < T; i += 64) P.out[g * T + i] = src[i];
-      }
+    if (kind == bfs::CODE_HALT) break;
+    if (kind == bfs::CODE_TRACK) {         // w1 producer engine, w2 instructions passed
+      const uint32_t a = snap + 4u * w1;
+      lds_store(a, uniform(lds_poll(a)) + w2);
+      pc += 1;
+      continue;
     }
-    // Retire in program order.
-    const int upd = P.instr_update[ins];
-    if (upd >= 0) retire_all_and_add(cnt_base + 4u * (uint32_t)(upd * bfs::kMaxWavesPerEngine), 1u);
-    else drain_all();
-    if (lane == 0) execn[ins] = inst + 1;
-    __builtin_amdgcn_s_waitcnt(0);
-    pc += 1;
+    {                                      // CODE_SNAP
+      // the producer engine's running count right after the producer's
+      // position, kept for the iteration of S it belongs to (w0: engine and
+      // S; w1 snapshots kept, w2 the first one's word)
+      const uint32_t idx = w1 > 1u ? umod(rl(rv, (w0 >> 16) & 0xffu), w1) : 0u;
+      lds_store(snap + 4u * (w2 + idx), uniform(lds_poll(snap + 4u * ((w0 >> 8) & 0xffu))));
+      pc += 1;
+      continue;
+    }
   }
-  if (P.dbg && lane == 0) P.dbg[(int64_t)wg * P.n_engines + wave] = nlog;
-  if (stt.on && lane == 0) {
+  retire_all();
+  if (kInstr && P.dbg && lane == 0) P.dbg[(int64_t)wg * P.n_engines + wave] = nlog;
+  if (kInstr && stt.on && lane == 0) {
     uint64_t *o = P.stats + ((int64_t)wg * P.n_engines + wave) * 8;
     o[0] = now_ticks() - stt.t_start;
     o[1] = stt.blocked;
@@ -263,14 +453,9 @@ bfs_status launch_interp(const bfs_plan *p, DevImage *img, const void *const *bu
   if (nbufs < 3) return fail(BFS_E_INVALID, "interpreter needs buffers [base, x, out]");
   InterpParams P{};
   P.code = img->code;
-  P.code_off = img->code_off;
+  P.engine_off = img->engine_off;
   P.waits = img->waits;
-  P.instr_waits = img->instr_waits;
-  P.waits_by_instr = img->waits_by_instr;
-  P.instr_opcode = img->instr_opcode;
-  P.instr_args = img->instr_args;
-  P.instr_update = img->instr_update;
-  P.loop_parent = img->loop_parent;
+  P.args = img->instr_args;
   P.trips = trips;
   P.trip_off = trip_off;
   P.base = static_cast<const int64_t *>(bufs[0]);
@@ -285,32 +470,49 @@ bfs_status launch_interp(const bfs_plan *p, DevImage *img, const void *const *bu
   P.fault_delta = o.fault_delta;
   P.n_loops = p->n_loops;
   P.n_engines = p->n_engines;
-  P.n_instrs = (int32_t)p->instr_engine.size();
-  P.mode = p->mode;
   P.fallback_loops = p->fallback_loops;
   P.tile = p->tile_elems > 0 ? p->tile_elems : 64;
-  int off = 0;
+  P.wide_x = P.tile == 256 && reinterpret_cast<uintptr_t>(bufs[1]) % 16 == 0;
+  P.wide_out = P.tile == 256 && reinterpret_cast<uintptr_t>(bufs[2]) % 16 == 0;
+  int64_t off = 0;
   for (int i = 0; i < 4; ++i) {
-    P.ring_off[i] = off;
-    off += p->ring_slots[i] * P.tile;
+    P.ring_off[i] = (int32_t)off;
+    off += (int64_t)p->ring_slots[i] * P.tile;
   }
-  P.acc_off = off;
-  off += (p->n_accs > 0 ? p->n_accs : 0) * P.tile;
+  P.acc_off = (int32_t)off;
+  off += (int64_t)(p->n_accs > 0 ? p->n_accs : 0) * P.tile;
+  const int64_t data_floats = off + 4 * P.tile;
+  P.data_floats = (int32_t)data_floats;
   const int counters_bytes = kMaxSlots * kMaxWavesPerEngine * 4;
-  P.lds_state_off = counters_bytes;
-  P.lds_exec_off = P.lds_state_off + p->n_engines * 3 * kMaxLoops * 4;
-  P.lds_data_off = P.lds_exec_off + p->n_engines * kMaxInstrsInterp * 4;
+  P.lds_data_off = counters_bytes;
   P.snap_words = p->mode == BFS_MODE_BARRIER_FREE && p->alloc == BFS_ALLOC_PER_ENGINE ? p->snap_words : 0;
-  P.lds_snap_off = P.lds_data_off + (off + 4 * P.tile) * 4;
+  P.lds_snap_off = (int32_t)(P.lds_data_off + data_floats * 4);
   const size_t lds_bytes = (size_t)P.lds_snap_off + (size_t)p->n_engines * P.snap_words * 4;
-  if (lds_bytes > 160 * 1024) return fail(BFS_E_RESOURCE, "interpreter: LDS footprint over 160 KiB");
-  hipError_t err = hipFuncSetAttribute((const void *)interp_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds_bytes);
-  if (err != hipSuccess) return fail(BFS_E_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(err));
-  hipLaunchKernelGGL(interp_kernel, dim3(n_wg), dim3(64 * p->n_engines), lds_bytes, (hipStream_t)stream, P);
-  err = hipGetLastError();
-  if (err != hipSuccess) return fail(BFS_E_DEVICE, std::string("interp launch: ") + hipGetErrorString(err));
-  return BFS_OK;
+  // The limit a program is held to includes 1408 bytes per engine for loop
+  // registers and per-instruction words, the family's documented footprint
+  // (they are held in registers).
+  if (lds_bytes + (size_t)p->n_engines * (3 * kMaxLoops + kMaxInstrsInterp) * 4 > 160 * 1024)
+    return fail(BFS_E_RESOURCE, "interpreter: LDS footprint over 160 KiB");
+  // the program in registers: at most 64 code words and 64 waits per engine
+  bool lanes = true;
+  for (int e = 0; e < p->n_engines; ++e)
+    lanes = lanes && p->code_off[e + 1] - p->code_off[e] <= 64 && img->n_waits[e] <= 64;
+  const bool instr = dbg || o.dev_stats || o.fault_dep >= 0;
+  auto go = [&](auto kern) -> bfs_status {
+    hipError_t err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (err != hipSuccess) return fail(BFS_E_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(err));
+    hipLaunchKernelGGL(kern, dim3(n_wg), dim3(64 * p->n_engines), lds_bytes, (hipStream_t)stream, P);
+    err = hipGetLastError();
+    if (err != hipSuccess) return fail(BFS_E_DEVICE, std::string("interp launch: ") + hipGetErrorString(err));
+    return BFS_OK;
+  };
+  if (p->mode == BFS_MODE_BARRIER) {
+    if (instr) return lanes ? go(interp_kernel<BFS_MODE_BARRIER, true, true>) : go(interp_kernel<BFS_MODE_BARRIER, true, false>);
+    return lanes ? go(interp_kernel<BFS_MODE_BARRIER, false, true>) : go(interp_kernel<BFS_MODE_BARRIER, false, false>);
+  }
+  if (instr)
+    return lanes ? go(interp_kernel<BFS_MODE_BARRIER_FREE, true, true>) : go(interp_kernel<BFS_MODE_BARRIER_FREE, true, false>);
+  return lanes ? go(interp_kernel<BFS_MODE_BARRIER_FREE, false, true>) : go(interp_kernel<BFS_MODE_BARRIER_FREE, false, false>);
 }
 
 }  // namespace bfs

@@ -56,7 +56,7 @@ std::vector<DevWait> device_waits(const bfs_plan *p) {
 namespace {
 
 // Table order in a packed plan image.
-enum { T_CODE, T_COFF, T_WAIT, T_OP, T_ARGS, T_IW, T_WL, T_UPD, T_LP, T_N };
+enum { T_CODE, T_EOFF, T_WAIT, T_ARGS, T_N };
 // The first kErrBytes of an image hold the error words (zero at upload).
 constexpr size_t kErrBytes = 256;
 
@@ -64,17 +64,47 @@ constexpr size_t kErrBytes = 256;
 // plan->dev_mu).
 void pack_tables(bfs_plan *plan) {
   if (!plan->packed.empty()) return;
-  const std::vector<DevWait> waits = device_waits(plan);
-  const std::pair<const void *, size_t> src[T_N] = {
-      {plan->code.data(), plan->code.size() * 4},
-      {plan->code_off.data(), plan->code_off.size() * 4},
-      {waits.data(), waits.size() * sizeof(DevWait)},
-      {plan->instr_opcode.data(), plan->instr_opcode.size() * 4},
-      {plan->instr_args.data(), plan->instr_args.size() * 4},
-      {plan->instr_wait_off.data(), plan->instr_wait_off.size() * 4},
-      {plan->instr_wait_list.data(), plan->instr_wait_list.size() * 4},
-      {plan->instr_update.data(), plan->instr_update.size() * 4},
-      {plan->loop_parent.data(), plan->loop_parent.size() * 4}};
+  const std::vector<DevWait> dw = device_waits(plan);
+  const int E = plan->n_engines;
+  std::vector<int32_t> code = plan->code, eoff(3 * (E + 1), 0), rows, waits;
+  for (int e = 0; e <= E; ++e) {
+    eoff[e] = plan->code_off[e];
+    eoff[E + 1 + e] = (int32_t)rows.size() / 8;
+    eoff[2 * (E + 1) + e] = (int32_t)waits.size() / 8;
+    if (e == E) break;
+    for (int32_t pc = plan->code_off[e]; pc < plan->code_off[e + 1]; ++pc) {
+      int32_t *w = &code[4 * (size_t)pc];
+      if (w[0] == CODE_LOOP) {
+        w[3] = plan->loop_parent[w[1]];
+      } else if (w[0] == CODE_SNAP) {
+        const DevWait &d = dw[w[1]];
+        w[0] |= d.prd_engine << 8 | d.loop_S << 16;
+        w[1] = d.snap_slots;
+        w[2] = d.snap_off;
+      } else if (w[0] == CODE_INSTR) {
+        const int32_t ins = w[1];
+        const int32_t op = plan->instr_opcode[ins];
+        const int32_t first = plan->instr_wait_off[ins], n = plan->instr_wait_off[ins + 1] - first;
+        w[0] |= (op >= 0 && op <= 5 ? op : 0) << 8 | plan->instr_parent[ins] << 16 | (plan->instr_update[ins] + 1) << 24;
+        w[1] = (int32_t)rows.size() / 8 - eoff[E + 1 + e];
+        w[2] = (int32_t)waits.size() / 8 - eoff[2 * (E + 1) + e];
+        w[3] = n;
+        rows.insert(rows.end(), &plan->instr_args[8 * (size_t)ins], &plan->instr_args[8 * (size_t)ins] + 8);
+        for (int32_t i = first; i < first + n; ++i) {
+          const DevWait &d = dw[plan->instr_wait_list[i]];
+          const int32_t v = plan->mode == BFS_MODE_BARRIER ? (d.active ? d.ordinal : 0) : d.snap_slots > 0 ? d.snap_off : d.expr_sub;
+          const int32_t row[8] = {d.counter | d.loop_P << 8 | d.loop_S << 16 | (d.needs_mask ? 1 : 0) << 24 |
+                                      (d.linear ? 1 : 0) << 25, d.dep, d.k, v, d.N, d.K, d.snap_slots, 0};
+          waits.insert(waits.end(), row, row + 8);
+        }
+      }
+    }
+    plan->packed_waits[e] = (int32_t)waits.size() / 8 - eoff[2 * (E + 1) + e];
+  }
+  const std::pair<const void *, size_t> src[T_N] = {{code.data(), code.size() * 4},
+                                                    {eoff.data(), eoff.size() * 4},
+                                                    {waits.data(), waits.size() * 4},
+                                                    {rows.data(), rows.size() * 4}};
   plan->packed_off.assign(T_N, 0);
   size_t off = kErrBytes;
   for (int t = 0; t < T_N; ++t) {
@@ -93,14 +123,10 @@ DevImage image_at(const bfs_plan *plan, void *mem, int dev) {
   img.device = dev;
   auto at = [&](int t) { return reinterpret_cast<unsigned char *>(mem) + plan->packed_off[t]; };
   img.code = reinterpret_cast<int32_t *>(at(T_CODE));
-  img.code_off = reinterpret_cast<int32_t *>(at(T_COFF));
-  img.waits = reinterpret_cast<DevWait *>(at(T_WAIT));
-  img.instr_opcode = reinterpret_cast<int32_t *>(at(T_OP));
+  img.engine_off = reinterpret_cast<int32_t *>(at(T_EOFF));
+  img.waits = reinterpret_cast<int32_t *>(at(T_WAIT));
   img.instr_args = reinterpret_cast<int32_t *>(at(T_ARGS));
-  img.instr_waits = reinterpret_cast<int32_t *>(at(T_IW));
-  img.waits_by_instr = reinterpret_cast<int32_t *>(at(T_WL));
-  img.instr_update = reinterpret_cast<int32_t *>(at(T_UPD));
-  img.loop_parent = reinterpret_cast<int32_t *>(at(T_LP));
+  for (int e = 0; e < kMaxEngines; ++e) img.n_waits[e] = plan->packed_waits[e];
   img.err = reinterpret_cast<uint32_t *>(mem);
   return img;
 }
