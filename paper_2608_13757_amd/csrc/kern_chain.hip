@@ -11,11 +11,22 @@
 // offset 0, CONS->LOAD at offset R (a slot is refilled only after its tile
 // was read, inside one trip of B), CONS->ACQ at offset 1 (case C3 at A: the
 // next trip of B starts filling slot 0 again only after the previous trip's
-// reads).  The load engine keeps up to four loads in flight (one 16-byte
-// direct-to-LDS load per lane moves a tile) and retires them in issue order
-// with counted vmcnt waits; the vector engine signals right after its ring
-// read returned.  Barrier mode synchronizes both waves before each loop
-// statement and at every iteration end, with static ordinals in a region.
+// reads).  Barrier mode synchronizes both waves before each loop statement
+// and at every iteration end, with static ordinals in a region.
+//
+// What bounds it: one workgroup runs a serial chain of hand-offs, so memory
+// latency must stay out of the chain.  The tiles of a workgroup are adjacent
+// in memory and their number is the sum of B's trips, so the load engine
+// fetches them ahead of the waits, kStage tiles in flight, by direct-to-LDS
+// loads (16 bytes per lane) into a staging ring that only it uses.  LOAD then
+// is a copy from staging to the ring slot, held in a register before the wait
+// of its slot, and retires at once (LDS executes the counter add after the
+// write).  The last loads of a workgroup repeat its last tile, so that the
+// counted vmcnt wait is the same for every tile.  The vector engine takes up
+// to four tiles that the last observed counter covers in one LDS round trip,
+// with one counter add.  One workgroup, 16 iterations of A, trips of B up to
+// 8: 16.9 us against 26.5 us with the loads issued after each wait into the
+// ring itself, which exposed the memory latency in every iteration of A.
 //
 // Family contract (BFS_KERNEL_CHAIN): loops top -> A -> B; engines of one
 // wave each; ACQ (opcode 0, E0) in A before B; LOAD (1, E0) and CONS (2, E1)
@@ -33,7 +44,7 @@ namespace {
 
 constexpr int kTileFloats = 256;
 constexpr uint32_t kTileBytes = kTileFloats * 4;
-constexpr uint32_t kMaxInflight = 4;
+constexpr uint32_t kStage = 8;           // tiles in flight ahead of the ring
 
 struct ChainParams {
   SyncCommon sc;
@@ -44,9 +55,15 @@ struct ChainParams {
   const float *x;
   float *out;
   int32_t ring;
-  uint32_t inflight;
   float scale;
 };
+
+// Sum over the 64 lanes, wave-uniform.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o);
+  return uniform(v);
+}
 
 template <int kMode, bool kInstr>
 __global__ void __launch_bounds__(128) chain_kernel(ChainParams P) {
@@ -65,89 +82,195 @@ __global__ void __launch_bounds__(128) chain_kernel(ChainParams P) {
   const int64_t off_b = ldc(toff + 2);
   const int64_t tbase = ldc(P.base + wg);
   const uint32_t R = (uint32_t)P.ring;
+  const uint32_t ring_l = lds_addr(ring) + 16u * lane;     // this lane's 16 bytes of slot 0
   Regs g;
+  // trips of B, 64 iterations of A at a time, one per lane
+  uint32_t trips_b = lane < trip_a ? (uint32_t)P.trips[off_b + lane] : 0u;
+  asm volatile("" : "+v"(trips_b));
+  auto trip_of = [&](uint32_t ia) {
+    if (ia > 0u && (ia & 63u) == 0u) {
+      trips_b = ia + lane < trip_a ? (uint32_t)P.trips[off_b + ia + lane] : 0u;
+      asm volatile("" : "+v"(trips_b));   // arrived here, so that no other iteration waits for loads in flight
+    }
+    return (uint32_t)__builtin_amdgcn_readlane((int)trips_b, (int)(ia & 63u));
+  };
+
+  // Barrier-free, uninstrumented launches: one compare with the last observed
+  // counter value per wait, then polls without sleeping (the two waves share
+  // no issue slots with others worth yielding to).
+  constexpr bool kLean = kMode == BFS_MODE_BARRIER_FREE && !kInstr;
+  const uint32_t limit = P.sc.watchdog > 0xffffffffull ? 0xffffffffu : (uint32_t)P.sc.watchdog;
+  auto affine = [](const Site<1> &st, uint32_t t) {    // threshold of iteration t (0: no wait)
+    const int32_t v = st.base[0] + (int32_t)((st.mk[0] >> 16) * t);
+    return st.n > 0u && t > (st.mk[0] & 0xffffu) && v > 0 ? (uint32_t)v : 0u;
+  };
+  // The waits of LOAD and CONS are on loop B's own iterations (producer and
+  // shared loop B): their base moves by N per iteration of B.
+  auto next_trip = [](Site<1> &st, uint32_t trip) { st.base[0] += (int32_t)((st.mk[0] >> 16) * trip); };
+  auto spin = [&](Site<1> &st, uint32_t thr, const InstrWaits &iw, uint32_t instance) __attribute__((always_inline)) {
+    if (thr <= st.seen[0] || S.aborted) return;
+    const uint32_t addr = st.meta[0] & 0xffffu;
+    for (uint32_t polls = 0;; ++polls) {
+      const uint32_t v = uniform(lds_poll(addr));
+      st.seen[0] = v;
+      if (v >= thr) return;
+      if (polls >= limit) {
+        report_deadlock(P.sc.err, iw.w[0].w.w3 & 0xffffu, (uint32_t)wg, instance, thr, v, (uint32_t)wave);
+        S.aborted = 1u;
+        return;
+      }
+      if (polls >= 256u) __builtin_amdgcn_s_sleep(2);
+    }
+  };
 
   if (wave == 0) {
     // ------------------------------------------------------------ load engine
-    uint32_t pending = 0;                  // loads issued, not yet retired
-    auto retire_one = [&]() {              // the oldest load has landed
-      wait_vm_dyn((int)pending - 1);
-      S.signal(P.load.update, 0);
-      pending -= 1;
+    // tiles of this workgroup: the sum of B's trips
+    uint32_t n_tiles = trips_b;
+    for (uint32_t i = lane + 64u; i < trip_a; i += 64u) n_tiles += (uint32_t)P.trips[off_b + i];
+    n_tiles = wave_sum(n_tiles);
+    const char *src = reinterpret_cast<const char *>(P.x + tbase * kTileFloats) + 16u * lane;
+    const uint32_t stage = lds_addr(ring) + R * kTileBytes, stage_l = stage + 16u * lane;
+    uint32_t fetch = 0, fslot = 0, tslot = 0;    // next tile to fetch and its staging slot; staging slot to read next
+    auto fetch_one = [&]() {
+      __builtin_amdgcn_global_load_lds((const void *)(src + (int64_t)min(fetch, n_tiles - 1u) * kTileBytes),
+                                       (BFS_LDS void *)(uintptr_t)(stage + fslot * kTileBytes), 16, 0, 0);
+      fetch += 1;
+      fslot = (fslot + 1u) % kStage;
     };
-    auto retire_all = [&]() {
-      if (pending > 0) {
-        wait_vm<0>();
-        for (uint32_t i = 0; i < pending; ++i) S.signal(P.load.update, 0);
-        pending = 0;
-      }
+    f32x4 tile = {};
+    // the oldest staged tile into registers (kStage loads are in flight, so
+    // at most kStage - 1 may remain), then its staging slot is refilled
+    auto take = [&]() {
+      asm volatile("s_waitcnt vmcnt(%2)\n\tds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                   : "=v"(tile)
+                   : "v"(stage_l + tslot * kTileBytes), "n"(kStage - 1)
+                   : "memory");
+      tslot = (tslot + 1u) % kStage;
+      fetch_one();
     };
-    const float *src = P.x + tbase * kTileFloats + 4 * lane;
+    if (n_tiles > 0) {
+      for (uint32_t i = 0; i < kStage; ++i) fetch_one();
+      take();
+    }
     Site<1> s_acq, s_load;
     S.sync_point(S.word(0, 0));                        // before loop A
-    S.enter(s_acq, P.acq, g, 1);
-    // the trip of B for the next iteration of A is fetched one iteration ahead
-    uint32_t trip_next = trip_a > 0 ? (uint32_t)ldc(P.trips + off_b) : 0u;
+    S.enter(s_acq, P.acq, g, 1);                       // (a C3 wait: evaluated at each iteration of A)
+    if (kLean) S.enter(s_load, P.load, g, 2);
     for (uint32_t ia = 0; ia < trip_a; ++ia) {
       g.r1 += 1;
       g.h1 = ia + 1;
-      const uint32_t trip_b = trip_next;
-      trip_next = (uint32_t)ldc(P.trips + off_b + min(ia + 1u, trip_a - 1u));
-      // ACQ: its waits; retired after everything before it
-      S.wait(s_acq, P.acq, g, ia + 1, g.r1 - 1, [&] { if (pending > 0) retire_one(); });
-      if (P.acq.update >= 0) {
-        retire_all();
+      const uint32_t trip_b = trip_of(ia);
+      if constexpr (kLean) {
+        // ACQ and LOAD by running thresholds; both mostly wait for CONS, so
+        // what ACQ observed serves LOAD too
+        if (P.acq.n > 0) spin(s_acq, S.threshold_plain(P.acq.w[0].w, g), P.acq, ia);
         S.signal(P.acq.update, 0);
+        if ((s_acq.meta[0] & 0xffffu) == (s_load.meta[0] & 0xffffu)) s_load.seen[0] = max(s_load.seen[0], s_acq.seen[0]);
+        uint32_t slot_l = ring_l;
+        for (uint32_t ib = 0; ib < trip_b; ++ib) {
+          spin(s_load, affine(s_load, ib + 1), P.load, g.r2 + ib);
+          asm volatile("ds_write_b128 %0, %1" ::"v"(slot_l), "v"(tile) : "memory");
+          S.signal(P.load.update, 0);
+          take();                                      // the next tile, before the waits it may have to pass
+          slot_l = slot_l + kTileBytes == ring_l + R * kTileBytes ? ring_l : slot_l + kTileBytes;
+        }
+        g.r2 += trip_b;
+        g.h2 = trip_b;
+        next_trip(s_load, trip_b);
+        continue;
       }
+      // ACQ: its waits; everything before it has retired
+      S.wait(s_acq, P.acq, g, ia + 1, g.r1 - 1, [] {});
+      S.signal(P.acq.update, 0);
       S.sync_point(S.word(0, 0));                      // before loop B
       S.enter(s_load, P.load, g, 2);
       uint32_t slot = 0;
       for (uint32_t ib = 0; ib < trip_b; ++ib) {
         g.r2 += 1;
         g.h2 = ib + 1;
-        S.wait_affine(s_load, P.load, g, ib + 1, g.r2 - 1, [&] { if (pending > 0) retire_one(); });
+        S.wait_affine(s_load, P.load, g, ib + 1, g.r2 - 1, [] {});
         if (!S.aborted) {
-          __builtin_amdgcn_global_load_lds((const void *)(src + (int64_t)(g.r2 - 1) * kTileFloats),
-                                           (BFS_LDS void *)(ring + slot * kTileBytes), 16, 0, 0);
-          pending += 1;
-          if (pending == P.inflight) retire_one();
+          asm volatile("ds_write_b128 %0, %1" ::"v"(ring_l + slot * kTileBytes), "v"(tile) : "memory");
+          S.signal(P.load.update, 0);
+          take();                                      // the next tile, before the waits it may have to pass
         } else {
           S.signal(P.load.update, 0);
         }
-        if (kMode == BFS_MODE_BARRIER) {
-          retire_all();
-          S.sync_point(S.word(0, 0));                  // end of a B iteration
-        }
+        S.sync_point(S.word(0, 0));                    // end of a B iteration (barrier mode)
         slot = (slot + 1 == R) ? 0u : slot + 1;
       }
-      // The trip's loads are all issued: retire them in order as they land,
-      // so the vector engine sees each tile as early as possible (the next
-      // ACQ waits for those tiles to be consumed anyway).
-      while (pending > 0) retire_one();
       S.sync_point(S.word(0, 0));                      // end of an A iteration
     }
-    retire_all();
   } else {
     // ---------------------------------------------------------- vector engine
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     const float c = P.scale;
     Site<1> s_cons, s_store;
+    if (kLean) S.enter(s_cons, P.cons, g, 2);
     S.sync_point(S.word(1, 0));                        // before loop A
-    uint32_t trip_next = trip_a > 0 ? (uint32_t)ldc(P.trips + off_b) : 0u;
     for (uint32_t ia = 0; ia < trip_a; ++ia) {
       g.r1 += 1;
       g.h1 = ia + 1;
-      const uint32_t trip_b = trip_next;
-      trip_next = (uint32_t)ldc(P.trips + off_b + min(ia + 1u, trip_a - 1u));
+      const uint32_t trip_b = trip_of(ia);
       S.sync_point(S.word(1, 0));                      // before loop B
-      S.enter(s_cons, P.cons, g, 2);
+      if (!kLean) S.enter(s_cons, P.cons, g, 2);
       uint32_t slot = 0;
+      if constexpr (kLean) {
+        // Tiles that the observed counter covers, four or two at a time: with
+        // one LOAD per count (N = 1) the threshold of iteration t is base + t.
+        const bool unit = (s_cons.mk[0] >> 16) == 1u && (s_cons.mk[0] & 0xffffu) == 0u && s_cons.n == 1u;
+        auto at = [&](uint32_t i) {                    // slot i places on
+          const uint32_t sl = slot + i;
+          return ring_l + (sl >= R ? sl - R : sl) * kTileBytes;   // (at most R tiles wait in the ring)
+        };
+        auto read = [&](uint32_t i) { return *(const BFS_LDS f32x4 *)(uintptr_t)at(i); };
+        auto add = [&](const f32x4 &v) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[j] = acc[j] + c * v[j];
+        };
+        // LDS executes the counter add after the reads before it
+        auto signal = [&](uint32_t k) {
+          if (P.cons.update >= 0) lds_add(S.word((uint32_t)P.cons.update, 0), k);
+        };
+        for (uint32_t ib = 0; ib < trip_b;) {
+          spin(s_cons, affine(s_cons, ib + 1), P.cons, g.r2 + ib);
+          const uint32_t have = S.aborted || !unit ? 1u : min(s_cons.seen[0] - (uint32_t)s_cons.base[0], trip_b) - ib;
+          uint32_t k = 1;
+          if (have >= 4u) {
+            k = 4;
+            const f32x4 v0 = read(0), v1 = read(1), v2 = read(2), v3 = read(3);
+            signal(4);
+            add(v0);
+            add(v1);
+            add(v2);
+            add(v3);
+          } else if (have >= 2u) {
+            k = 2;
+            const f32x4 v0 = read(0), v1 = read(1);
+            signal(2);
+            add(v0);
+            add(v1);
+          } else {
+            const f32x4 v0 = read(0);
+            signal(1);
+            add(v0);
+          }
+          ib += k;
+          slot += k;
+          if (slot >= R) slot -= R;
+        }
+        g.r2 += trip_b;
+        g.h2 = trip_b;
+        next_trip(s_cons, trip_b);
+        continue;
+      }
       for (uint32_t ib = 0; ib < trip_b; ++ib) {
         g.r2 += 1;
         g.h2 = ib + 1;
         S.wait_affine(s_cons, P.cons, g, ib + 1, g.r2 - 1, [] {});
         if (!S.aborted) {
-          const f32x4 v = *(const BFS_LDS f32x4 *)(uintptr_t)(lds_addr(ring) + slot * kTileBytes + 16u * lane);
+          const f32x4 v = *(const BFS_LDS f32x4 *)(uintptr_t)(ring_l + slot * kTileBytes);
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[j] = acc[j] + c * v[j];
         }
@@ -233,9 +356,8 @@ bfs_status launch_chain(const bfs_plan *p, DevImage *img, const void *const *buf
   P.out = static_cast<float *>(const_cast<void *>(bufs[2]));
   P.sc = sync_common(img, dbg, dbg_cap, o, 2);
   P.ring = R;
-  P.inflight = (uint32_t)R < kMaxInflight ? (uint32_t)R : kMaxInflight;
   P.scale = __builtin_bit_cast(float, ca[7]);
-  const size_t lds = kCntBytes + (size_t)R * kTileBytes;
+  const size_t lds = kCntBytes + (size_t)(R + kStage) * kTileBytes;
   const bool instr = dbg || o.dev_stats || o.fault_dep >= 0;
   hipStream_t s = (hipStream_t)stream;
   auto go = [&](auto kern) -> bfs_status {
