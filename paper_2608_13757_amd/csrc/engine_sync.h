@@ -120,7 +120,10 @@ __device__ __forceinline__ uint32_t min16(uint32_t v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-template <int kMode, bool kInstr>
+// kSpin: repeated polls of a blocked wait before it starts to sleep between
+// them (kernels whose hand-off latency matters more than the issue slots).
+// kMulti: every producer engine has several waves (no code for one).
+template <int kMode, bool kInstr, uint32_t kSpin = 0, bool kMulti = false>
 struct Sync {
   const SyncCommon &C;
   uint32_t cnt_base;
@@ -152,7 +155,7 @@ struct Sync {
   template <class OnBlock>
   __device__ __forceinline__ uint32_t poll_geq(uint32_t addr, uint32_t nw, uint32_t thr, uint32_t dep,
                                                uint32_t instance, OnBlock on_block) {
-    if (nw == 1) {
+    if (!kMulti && nw == 1) {
       // one producer wave: a scalar compare of its word
       uint32_t v = uniform(lds_poll(addr));
       if (v >= thr) return v;
@@ -169,7 +172,8 @@ struct Sync {
           aborted = 1u;
           return v;
         }
-        if (polls < 4) __builtin_amdgcn_s_sleep(1);
+        if (kSpin > 0 && polls < kSpin) continue;
+        if (polls < kSpin + 4) __builtin_amdgcn_s_sleep(1);
         else __builtin_amdgcn_s_sleep(2);
       }
       if (kInstr && st.on) {
@@ -197,7 +201,8 @@ struct Sync {
         aborted = 1u;
         return m;
       }
-      if (polls < 4) __builtin_amdgcn_s_sleep(1);
+      if (kSpin > 0 && polls < kSpin) continue;
+      if (polls < kSpin + 4) __builtin_amdgcn_s_sleep(1);
       else __builtin_amdgcn_s_sleep(2);
     }
     if (kInstr && st.on) {

@@ -48,52 +48,12 @@
 #include <string>
 #include <type_traits>
 
-#include "engine_sync.h"
+#include "gemm_common.h"
 
 using namespace bfsdev;
+using namespace bfsgemm;
 
 namespace {
-
-constexpr int kTile = 256, kBK = 32;
-constexpr int kLoadW = 2, kMmaW = 8, kEpiW = 2, kWaves = 12;
-constexpr uint32_t kSlotBytes = 2 * kTile * kBK * 2;     // A + B of one K step
-constexpr uint32_t kESlotBytes = kMmaW * 32 * 32 * 2;     // 8 bf16 blocks
-constexpr int kMaxSteps = 128;                            // K steps of the K-unrolled program
-
-struct GemmParams {
-  SyncCommon sc;
-  InstrWaits bias, load, mma, spill, epi;
-  const __bf16 *a;
-  const __bf16 *bt;
-  const float *bias_v;
-  __bf16 *c;
-  const int32_t *trips;
-  const int64_t *trip_off;
-  int32_t m, n, k;
-  int32_t ring, e_ring;
-  int32_t tiles_m, tiles_n;
-  int32_t xcd_map;          // 1: group tiles per XCD
-  int32_t n_loops;          // 3 (top, K, C) or 2 (top, C: the K-unrolled program)
-  // K-unrolled program: counter slots of the top-level LOAD and MMA
-  // instructions, and the dependency id of each step's wait (debug log)
-  int32_t c_load, c_mma;
-  uint16_t dep_mma[kMaxSteps], dep_load[kMaxSteps];
-};
-
-__device__ __forceinline__ float gelu_erf(float x) {
-  const float z = x * 0.70710678118654752f;
-  const float a = __builtin_fabsf(z);
-  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * a);
-  const float poly =
-      t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-  const float erf_a = 1.0f - poly * __expf(-a * a);
-  const float erf_z = __builtin_copysignf(erf_a, z);
-  return 0.5f * x * (1.0f + erf_z);
-}
-
-__device__ __forceinline__ uint32_t swz(uint32_t row, uint32_t chunk) {
-  return row * 64u + ((chunk ^ ((row >> 2) & 3u)) << 4);
-}
 
 // kUnroll: K steps per copy of the load and MFMA loop bodies (the trip of
 // loop K is static, so an unrolled body sees its thresholds as fixed offsets
@@ -530,6 +490,8 @@ bfs_status launch_gemm(const bfs_plan *p, DevImage *img, const void *const *bufs
   const size_t lds = kCntBytes + (size_t)ring * kSlotBytes + 1024;
   const bool instr = dbg || o.dev_stats || o.fault_dep >= 0;
   hipStream_t s = (hipStream_t)stream;
+  bfs_status st = BFS_OK;
+  if (p->mode == BFS_MODE_BARRIER_FREE && !instr && !flat && o.k_unroll == 1 && launch_parts(P, n_wg, s, st)) return st;
   auto go = [&](auto kern) -> bfs_status {
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return fail(BFS_E_DEVICE, std::string("gemm attribute: ") + hipGetErrorString(e));
