@@ -125,6 +125,21 @@ __device__ __forceinline__ uint32_t min16(uint32_t v) {
 // kMulti: every producer engine has several waves (no code for one).
 template <int kMode, bool kInstr, uint32_t kSpin = 0, bool kMulti = false>
 struct Sync {
+  // A wave-uniform value the compiler must take as new here: what is derived
+  // from it is computed where it is used instead of being hoisted out of the
+  // loops, where the masks and differences of a few waits fill the scalar
+  // registers (spilled into vector registers, next to the accumulators).
+  // Only where a spin count is given: other kernels keep what they hoist.
+  __device__ __forceinline__ static uint32_t here(uint32_t v) {
+    if (kSpin == 0) return v;
+    v = uniform(v);
+    asm volatile("" : "+s"(v));
+    return v;
+  }
+  __device__ __forceinline__ static bfs::PackedWait here(const bfs::PackedWait &w) {
+    return bfs::PackedWait{here(w.w0), here(w.w1), here(w.w2), here(w.w3)};
+  }
+
   const SyncCommon &C;
   uint32_t cnt_base;
   int wave, wg;            // wave: engine-ordered index (debug log, stats)
@@ -217,15 +232,15 @@ struct Sync {
   // trips).
   template <int kN>
   __device__ __forceinline__ void enter(Site<kN> &s, const InstrWaits &iw, const Regs &g, uint32_t L) {
-    s.n = (uint32_t)iw.n;
+    s.n = here((uint32_t)iw.n);
     // Every element is assigned unconditionally (selects, no stores under
     // branches): stores of different elements merged across branches would
     // index the arrays dynamically and move them to scratch memory.
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      const bool on = j < iw.n;
-      const bfs::PackedWait w = iw.w[j].w;
-      uint32_t kind = (uint32_t)iw.w[j].kind;
+      const bool on = (uint32_t)j < s.n;
+      const bfs::PackedWait w = here(iw.w[j].w);
+      uint32_t kind = here((uint32_t)iw.w[j].kind);
       int32_t base = s.base[j];
       uint32_t mk = s.mk[j];
       if (kMode == BFS_MODE_BARRIER) {
@@ -269,7 +284,7 @@ struct Sync {
         } else if (kind == (uint32_t)kWaitConst) {
           thr = (uint32_t)s.base[j];
         } else {
-          thr = threshold_plain(iw.w[j].w, g);
+          thr = threshold_plain(here(iw.w[j].w), g);
         }
         uint32_t dep = 0;
         if (kInstr) {

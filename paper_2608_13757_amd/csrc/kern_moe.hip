@@ -63,40 +63,12 @@
 #include <string>
 #include <type_traits>
 
-#include "engine_sync.h"
+#include "moe_common.h"
 
 using namespace bfsdev;
+using namespace bfsmoe;
 
 namespace {
-
-constexpr int kBK = 32;
-constexpr int kLoadW = 2, kMmaW = 8, kEpiW = 2, kWaves = 12;
-// ring slot: the token rows of one K step (8 KiB for M-tiles of 128 rows,
-// 16 KiB for 256), then 256 weight rows (16 KiB)
-constexpr uint32_t a_slot_bytes(int bm) { return (uint32_t)bm * kBK * 2; }
-constexpr uint32_t slot_bytes(int bm) { return a_slot_bytes(bm) + 256 * kBK * 2; }
-constexpr uint32_t kESlotBytes = kMmaW * 32 * 32 * 2;
-
-struct MoeParams {
-  SyncCommon sc;
-  InstrWaits acql, load, mma, acqe, spill, epi;
-  const int32_t *work;
-  const int32_t *perm;
-  const int32_t *eoff;
-  const __bf16 *a;          // x (phase 1) or h (phase 2)
-  const __bf16 *w0;         // W_gate (phase 1) or W_down (phase 2)
-  const __bf16 *w1;         // W_up (phase 1)
-  __bf16 *out;              // h (phase 1) or y (phase 2)
-  const int32_t *trips;
-  const int64_t *trip_off;
-  int32_t kdim, ndim, ring, e_ring, n_experts, n_tokens;
-};
-
-__device__ __forceinline__ uint32_t swz(uint32_t row, uint32_t chunk) {
-  return row * 64u + ((chunk ^ ((row >> 2) & 3u)) << 4);
-}
-
-__device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // kBM: token rows per M-tile.  128: each MFMA wave holds a 64-row sub-tile
 // (two row blocks); 256: a 128-row sub-tile (four row blocks), twice the MFMA
@@ -591,6 +563,9 @@ bfs_status launch_moe(const bfs_plan *p, DevImage *img, const void *const *bufs,
     return BFS_OK;
   };
   const bool bar = p->mode == BFS_MODE_BARRIER;
+  bfs_status st = BFS_OK;
+  // barrier-free, uninstrumented: in units of the work items (kern_moe_part.hip)
+  if (!bar && !instr && launch_parts(P, phase, bm, ring_linear, n_wg, s, st)) return st;
   auto pick = [&](auto ph, auto bmc) -> bfs_status {
     constexpr int kP = decltype(ph)::value, kB = decltype(bmc)::value;
     if (bar)

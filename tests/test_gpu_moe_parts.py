@@ -1,0 +1,70 @@
+"""MoE grouped GEMM in units of work items (barrier-free, uninstrumented)
+against the same program instrumented, which runs whole items one step at a
+time: every element has the same order of K in both, so the outputs are equal
+bit for bit.  (The instrumented run against the fp64 oracle is
+test_gpu_moe.py's.)"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_13757_amd import ALLOC_PER_INSTR, ALLOC_PER_LOOP, MODE_BARRIER_FREE, Plan, bfs  # noqa: E402
+from tests.gpu_util import trip_tensors  # noqa: E402
+from workloads import moe_program, moe_worklist  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+RAGGED = [300, 0, 129, 1, 530, 33, 256, 31]
+# (counts, K, N, bm, mchunk, options); N is a multiple of both phases' tiles.
+# Quarters where 2 sum ceil(rows / 128) N-tiles <= 256, whole units of several
+# workgroups up to 512 items, of one beyond; K steps: one, odd, even.
+CASES = {
+    "quarters": (RAGGED, 256, 256, 256, None, {}),
+    "quarters_one_step": (RAGGED, 32, 256, 256, None, {}),
+    "quarters_odd_k": (RAGGED, 352, 256, 256, None, {"ring": 2, "e_ring": 1}),
+    "quarters_128_linear": (RAGGED, 320, 256, 128, 2, {"linear": True}),
+    "quarters_one_row": ([1], 96, 256, 256, None, {}),
+    "split": ([1100, 900, 255, 257, 64, 1, 0, 700], 224, 1280, 256, None, {}),
+    "split_two_slots": ([1100, 900, 255, 257, 64, 1, 0, 700], 128, 1280, 256, 3, {"ring": 2, "e_ring": 2}),
+    "split_odd_ring": ([1100, 900, 255, 257, 64, 1, 0, 700], 96, 1280, 256, 9, {"ring": 3, "e_ring": 1}),
+    "split_one_step": ([1100, 900, 255, 257, 64, 1, 0, 700], 32, 1280, 256, None, {"linear": False}),
+    "split_128": ([1100, 900, 255, 257, 64, 1, 0, 700], 288, 1280, 128, None, {}),
+    "split_128_ring": ([1100, 900, 255, 257, 64, 1, 0, 700], 160, 1280, 128, 3, {"ring": 4, "e_ring": 0}),
+    "split_linear": ([1100, 900, 255, 257, 64, 1, 0, 700], 192, 1280, 256, None, {"linear": True}),
+    "items": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 160, 16384, 256, 1, {}),
+    "items_128_linear": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 192, 16384, 128, 2, {"linear": True, "e_ring": 1}),
+    "linear_odd_k": (RAGGED, 96, 256, 256, None, {"linear": True}),      # stays whole
+}
+
+
+@pytest.mark.parametrize("alloc", [ALLOC_PER_LOOP, ALLOC_PER_INSTR])
+@pytest.mark.parametrize("phase", [1, 2])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_moe_units_equal_items(case, phase, alloc):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    bfs.lib()
+    counts, k, n, bm, mchunk, opt = CASES[case]
+    tokens = sum(counts)
+    g = torch.Generator(device="cuda").manual_seed(7)
+
+    def rand(*shape):
+        return torch.randn(*shape, generator=g, device="cuda").to(torch.bfloat16)
+
+    hidden, ffn = (k, n) if phase == 1 else (n, k)
+    perm = torch.randperm(tokens, generator=g, device="cuda").to(torch.int32)
+    eoff = torch.tensor(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32), device="cuda")
+    wl = moe_worklist(counts, phase, hidden, ffn, mchunk=mchunk, bm=bm)
+    trips, toff = trip_tensors(wl.trips)
+    plan = Plan(moe_program(phase, hidden, ffn, bm=bm, **opt), MODE_BARRIER_FREE, alloc)
+    weights = [rand(len(counts), n, k) for _ in range(2 if phase == 1 else 1)]
+    ins = [torch.from_numpy(wl.work.reshape(-1)).cuda(), perm, eoff, rand(tokens, k), *weights]
+    outs = []
+    for cap in (0, 4):
+        out = torch.full((tokens, n), -1, dtype=torch.int16, device="cuda")
+        log = torch.zeros(plan.debug_log_words(wl.trips.n_wg, cap), dtype=torch.int32, device="cuda") if cap else None
+        plan.run(ins + [out], trips, toff, wl.trips.n_wg, debug_log=log, debug_capacity=cap)
+        plan.status()
+        outs.append(out)
+    assert torch.isfinite(outs[1].view(torch.bfloat16).float()).all()
+    assert torch.equal(outs[0], outs[1])
