@@ -78,61 +78,67 @@ __device__ __forceinline__ void run_part(const GemmParams &P, unsigned char *lds
     // BIAS: 16 bytes from each of kTN / 4 lanes; it lands with the first pair of steps and retires before it
     if (wave == 0 && !S.aborted && lane < (uint32_t)kTN / 4u)
       __builtin_amdgcn_global_load_lds((const void *)(P.bias_v + n0 + 4 * lane), (BFS_LDS void *)(uintptr_t)bias_l, 16, 0, 0);
-    // The two waves take the pairs of steps in turn, A and B rows both, so
-    // that neither waits for a landed load while the other's slots come free.
-    // A wave has no part in the other's pairs: those retire on it at once, in
-    // order (its counter word counts every LOAD).
+    // Whole tiles: each wave loads half of every pair (64 KiB for one wave take
+    // longer to issue than the other pair's MFMAs last; 256 tiles, K = 4096:
+    // 129 us with a pair per wave, 124 split).  Smaller parts: the two waves
+    // take the pairs in turn, so that neither waits for a landed load while
+    // the other's slots come free (64 tiles in quarters, K = 2048: 32.1 us,
+    // split 32.9).  A wave has no part in the other's pairs: those retire on
+    // it at once, in order (its counter word counts every LOAD).
+    constexpr bool kBoth = kTM == kTile && kTN == kTile;
+    constexpr uint32_t kRows = kBoth ? 16u : 8u, kStep = kBoth ? 2u : 4u;   // rows per load, K steps per pass
     S.enter(s_load, P.load, g, 1);
     const char *abase = reinterpret_cast<const char *>(P.a + (size_t)m0 * P.k);
     const char *bbase = reinterpret_cast<const char *>(P.bt + (size_t)n0 * P.k);
-    // load j: rows 8 j + lane / 8 and the chunk that belongs at position
+    // load j: rows kRows j + r_in and the chunk that belongs at position
     // lane % 8; a single last step (n = 1): the lanes of its second half, which
     // K does not have, read the first half's bytes again (never used)
-    constexpr int kALoads = kTM / 8, kBLoads = kTN / 8;
-    const uint32_t r_in = lane >> 3;
+    constexpr int kALoads = kTM / (int)kRows, kBLoads = kTN / (int)kRows;
+    const uint32_t r_in = (kBoth ? 8u * ew : 0u) + (lane >> 3);
     uint32_t voff[kALoads];
     auto offsets = [&](uint32_t n) __attribute__((always_inline)) {
       const uint32_t keep = n == 1u ? 3u : 7u;
 #pragma unroll
       for (int j = 0; j < kALoads; ++j) {
-        const uint32_t chunk = (lane & 7u) ^ (((8u * j + r_in) >> 1) & 7u);
-        voff[j] = ((8u * j + r_in) * (uint32_t)P.k + 8u * (chunk & keep)) * 2u;
+        const uint32_t row = kRows * j + r_in, chunk = (lane & 7u) ^ ((row >> 1) & 7u);
+        voff[j] = (row * (uint32_t)P.k + 8u * (chunk & keep)) * 2u;
       }
     };
     offsets(2u);
-    const uint32_t one_pair = (uint32_t)P.ring == 2u ? 1u : 0u;
+    const uint32_t last_slot = (uint32_t)P.ring / 2u - 1u;         // slot pairs: one or two
     auto retire = [&](uint32_t n) {
       if (P.load.update >= 0 && n > 0) lds_add(S.word((uint32_t)P.load.update, ew), n);
     };
-    if (ew == 1u || trip_k == 0u) {
+    const uint32_t first = kBoth ? 0u : 2u * ew;
+    if (first != 0u || trip_k == 0u) {
       wait_vm<0>();
       S.signal(P.bias.update, ew);
     }
-    if (ew == 1u) retire(min(trip_k, 2u));             // pair 0 is wave 0's
-    for (uint32_t it = 2u * ew; it < trip_k; it += 4) {
+    if (first != 0u) retire(min(trip_k, 2u));          // pair 0 is wave 0's
+    for (uint32_t it = first; it < trip_k; it += kStep) {
       const uint32_t n = min(trip_k - it, 2u);
       g.r1 = it + n;
       g.h1 = it + n;
       S.wait_affine(s_load, P.load, g, it + n, it + n - 1u, [] {});
       if (!S.aborted) {
-        const uint32_t dst = ring + (one_pair ? 0u : ew * 2u * G::kSlot);
+        const uint32_t dst = ring + ((it >> 1) & last_slot) * 2u * G::kSlot + (kBoth ? 1024u * ew : 0u);
         const size_t kb = (size_t)it * (kBK * 2);
         if (n == 1u) offsets(1u);
 #pragma unroll
         for (int j = 0; j < kALoads; ++j) {
           asm volatile("" : "+v"(voff[j]));   // keep the offset a 32-bit value at its use
-          __builtin_amdgcn_global_load_lds((const void *)(abase + kb + voff[j]), (BFS_LDS void *)(uintptr_t)(dst + j * 1024u), 16, 0, 0);
+          __builtin_amdgcn_global_load_lds((const void *)(abase + kb + voff[j]), (BFS_LDS void *)(uintptr_t)(dst + j * (kRows * 128u)), 16, 0, 0);
         }
 #pragma unroll
         for (int j = 0; j < kBLoads; ++j) {
           asm volatile("" : "+v"(voff[j]));
           __builtin_amdgcn_global_load_lds((const void *)(bbase + kb + voff[j]),
-                                           (BFS_LDS void *)(uintptr_t)(dst + 2u * G::kASlot + j * 1024u), 16, 0, 0);
+                                           (BFS_LDS void *)(uintptr_t)(dst + 2u * G::kASlot + j * (kRows * 128u)), 16, 0, 0);
         }
         wait_vm<0>();
       }
       if (it == 0u) S.signal(P.bias.update, ew);
-      retire(n + min(trip_k - it - n, 2u));            // and the other wave's next pair
+      retire(n + (kBoth ? 0u : min(trip_k - it - n, 2u)));         // and the other wave's next pair
     }
   } else if (wave < kLoadW + kMmaW) {
     // ------------------------------------------------------------ MFMA engine
@@ -385,9 +391,9 @@ __global__ void __launch_bounds__(768) gemm_mixed_kernel(GemmParams P) {
 // tiles, halves, quarters on 256 compute units):
 //   64 tiles    95 (27)   64 (19)   52 (14)     a quarter each: one round
 //   128 tiles  100 (29)   76 (21)  103 (26)     a half each: one round
-//   168 tiles  102 (29)  132 (36)  147 (36)     whole tiles: one round
+//   168 tiles   97 (28)  132 (36)  147 (36)     whole tiles: one round
 // Beyond 256 tiles the last round of whole tiles, if it leaves half of the
-// compute units or more idle, runs in parts by the same rule (272 tiles: 163
+// compute units or more idle, runs in parts by the same rule (272 tiles: 160
 // against 207 us in two rounds of whole tiles).
 bool bfsgemm::launch_parts(GemmParams &P, int n_wg, hipStream_t s, bfs_status &st) {
   constexpr int kCUs = 256;
