@@ -108,6 +108,22 @@ struct Site {
   }
 };
 
+// The waits of one instruction in an engine loop, evaluated by lanes: lane
+// 16 j + w holds producer wave w of wait j (the word's address, the constant
+// part of Eq. 5 and, as in Site, mask offset and N), other lanes repeat wave 0
+// of a wait.  One LDS read, one comparison and one ballot then decide all
+// waits of the iteration, without scalar registers that live through the loop.
+// Instrumented and barrier builds use the Site inside.
+template <int kN>
+struct LaneSite {
+  static_assert(kN <= 4, "16 lanes per wait");
+  Site<kN> site;
+  uint32_t addr = 0;
+  int32_t base = 0;
+  uint32_t mk = 0;
+  bool consts = false;     // a wait that is constant during a trip
+};
+
 // Minimum of v over lanes 0 .. 15 with DPP moves (no LDS traffic), read from
 // lane 0.  The counter polls put producer wave w's word in lane w and repeat
 // lane 0's word in every lane at or above the producer count, so this is the
@@ -325,6 +341,103 @@ struct Sync {
             s.seen[j] = poll_geq(s.meta[j] & 0xffffu, (s.meta[j] >> 16) & 0xfu, thr, iw.w[j].w.w3 & 0xffffu,
                                  instance, on_block);
         }
+      }
+    }
+  }
+
+  template <int kN>
+  __device__ __forceinline__ void enter(LaneSite<kN> &s, const InstrWaits &iw, const Regs &g, uint32_t L) {
+    if constexpr (kMode == BFS_MODE_BARRIER || kInstr) {
+      enter(s.site, iw, g, L);
+    } else {
+      const uint32_t n = here((uint32_t)iw.n), lane = lane_id(), grp = lane >> 4;
+      s.addr = word(0, 0);
+      s.base = 0;
+      s.mk = 0;
+      s.consts = false;
+#pragma unroll
+      for (int j = 0; j < kN; ++j) {
+        if ((uint32_t)j < n) {
+          const bfs::PackedWait w = here(iw.w[j].w);
+          const int32_t N = (int32_t)(w.w1 & 0xffffu), K = (int32_t)(w.w1 >> 16);
+          int32_t base;
+          uint32_t mk;
+          if (here((uint32_t)iw.w[j].kind) == (uint32_t)kWaitAffine) {
+            base = N * ((int32_t)g.r(L) - (int32_t)(w.w2 >> 16)) - (N - K);
+            mk = (((w.w0 >> 24) & 1u) ? (w.w2 & 0xffffu) : 0u) | ((uint32_t)N << 16);
+          } else {                                     // a constant: slope 0, no mask
+            base = (int32_t)threshold_plain(w, g);
+            mk = 0;
+            s.consts = true;
+          }
+          const uint32_t wv = lane & 15u, nw = (uint32_t)iw.w[j].n_prd_waves;
+          const uint32_t addr = word(w.w0 & 0xffu, wv < nw ? wv : 0u);
+          const bool mine = grp == (uint32_t)j || (j == 0 && grp >= n);
+          s.addr = mine ? addr : s.addr;
+          s.base = mine ? base : s.base;
+          s.mk = mine ? mk : s.mk;
+        }
+      }
+      // (in registers as they are: not recomputed in the loop)
+      asm volatile("" : "+v"(s.addr), "+v"(s.base), "+v"(s.mk));
+    }
+  }
+
+  // The next trip of the loop, the last one of n iterations (the first trip: n
+  // = 0, after enter() before the loops around it): Eq. 5's part of earlier
+  // trips grows by N per iteration; constants are evaluated again.
+  template <int kN>
+  __device__ __forceinline__ void next_trip(LaneSite<kN> &s, const InstrWaits &iw, const Regs &g, uint32_t L, uint32_t n) {
+    if constexpr (kMode == BFS_MODE_BARRIER || kInstr) {
+      enter(s.site, iw, g, L);
+    } else {
+      s.base += (int32_t)((s.mk >> 16) * n);
+      if (s.consts) {
+        const uint32_t lane = lane_id(), grp = lane >> 4, nw = here((uint32_t)iw.n);
+#pragma unroll
+        for (int j = 0; j < kN; ++j)
+          if ((uint32_t)j < nw && here((uint32_t)iw.w[j].kind) == (uint32_t)kWaitConst) {
+            const int32_t base = (int32_t)threshold_plain(here(iw.w[j].w), g);
+            s.base = grp == (uint32_t)j || (j == 0 && grp >= nw) ? base : s.base;
+          }
+      }
+    }
+  }
+
+  // The words of a LaneSite as they are now, for a later wait_affine: counters
+  // only grow, so a threshold they reach stays reached, and the read is in
+  // flight while the wave does something else.
+  template <int kN>
+  __device__ __forceinline__ uint32_t peek(const LaneSite<kN> &s) const {
+    if constexpr (kMode == BFS_MODE_BARRIER || kInstr) return 0u;
+    return *(volatile BFS_LDS uint32_t *)(uintptr_t)s.addr;
+  }
+
+  // wait_affine on a LaneSite: kSpin polls of a blocked wait, then the
+  // general wait with its sleeps and watchdog.  seen: words from peek().
+  template <int kN, class OnBlock>
+  __device__ __forceinline__ void wait_affine(LaneSite<kN> &s, const InstrWaits &iw, const Regs &g, uint32_t t,
+                                              uint32_t instance, OnBlock on_block, uint32_t seen = 0) {
+    if constexpr (kMode == BFS_MODE_BARRIER || kInstr) {
+      wait(s.site, iw, g, t, instance, on_block);
+    } else {
+      if (aborted) return;
+      const int32_t v = s.base + (int32_t)((s.mk >> 16) * t);
+      const uint32_t thr = (t > (s.mk & 0xffffu) && v > 0) ? (uint32_t)v : 0u;
+      if (__ballot(seen < thr) == 0ull) {
+        asm volatile("" ::: "memory");     // (no access of the instruction before the test)
+        return;
+      }
+      for (uint32_t polls = 0; polls <= kSpin; ++polls) {
+        if (__ballot(lds_poll(s.addr) < thr) == 0ull) return;
+        on_block();
+      }
+#pragma unroll 1
+      for (int j = 0; j < iw.n; ++j) {
+        const bfs::PackedWait w = here(iw.w[j].w);
+        const uint32_t th = threshold_plain(w, g);
+        if (!aborted && th > 0)
+          poll_geq(word(w.w0 & 0xffu, 0), (uint32_t)iw.w[j].n_prd_waves, th, w.w3 & 0xffffu, instance, on_block);
       }
     }
   }

@@ -12,10 +12,10 @@
 //                          base-2 domain: running max m, rescale factor
 //                          alpha = 2^(m_old - m_new), P = 2^(S c - m_new)
 //                          written as bf16 over S in place, running sum l.
-//   E3 (4 waves, MFMA)     PREAD: the P fragments and alpha of the wave's 32
-//                          query rows into registers; PV: O = alpha O + P V
-//                          (fp32 accumulators); after each tile's KV loop
-//                          NORM: O / l to HBM.
+//   E3 (4 waves, MFMA)     PREAD: the P fragments and alpha of 64 query rows
+//                          into registers; PV: O = alpha O + P V for these
+//                          rows and 64 columns per wave (fp32 accumulators);
+//                          after each tile's KV loop NORM: O / l to HBM.
 //   E4 (1 wave, V load)    LOADV: the V block into a V ring slot.
 //
 // Loops top -> T -> KV: T runs the workgroup's tiles, KV ceil(L / 64) steps
@@ -60,6 +60,20 @@
 // from two ds_read_b64_tr_b16: within each group of 16 lanes, lane i receives
 // element i % 4 of the 8 bytes addressed by lane 4 j + i / 4 as its element j.
 //
+// What bounds a KV step (2600 cycles where its MFMAs take 1024): each engine's
+// own chain of waits, LDS accesses and arithmetic.  The QK waves are busy all
+// the time (16 stores of S at 28 cycles and more each, MFMAs, two waits of 250
+// to 350 cycles), and the two-slot rings behind them (K block: issue and
+// latency of its loads; S/P slot: softmax and PREAD) come close to their rate.
+// Hence, barrier-free: waits decided by lanes in one LDS read; QK's stores
+// under its MFMAs, K and V fragments read several MFMAs ahead, the S/P slot
+// waited for after half of QK's MFMAs, PREAD's and PV's waits joined.
+// us, before and after: 32 sequences of 128 .. 4096, 16 heads: 1693, 1571; 2 of
+// 16384: 5455, 4970 (1.33, 1.21 per step).  Slower: QK retiring a step under
+// the next step's MFMAs (K blocks are released later, 1.43 per step), K blocks
+// staged in registers (1.28; with both 1.29), other maps of waves to SIMDs
+// (1.28 .. 1.33), softmax waves at a higher priority (1.33).
+//
 // Family contract (BFS_KERNEL_ATTN): loop T below the top level and loop KV
 // in T, KV holding LOADK (E0, opcode 32, args [0, K ring depth, heads,
 // 128]), LOADV (E4, opcode 32, args [1, V ring depth, heads, 128]), QK (E1,
@@ -84,11 +98,14 @@ constexpr int kD = 128, kBQ = 128, kBKV = 64;
 constexpr int kWaves = 12;
 constexpr uint32_t kKVSlot = kBKV * kD * 2;      // 16 KiB
 constexpr uint32_t kSPSlot = kBQ * kBKV * 4;     // 32 KiB
+constexpr uint32_t kSpinPolls = 32;
 constexpr int kMaxPend = 3;                      // load groups in flight per load wave
 
 struct AttnParams {
   SyncCommon sc;
   InstrWaits loadk, loadv, qk, sm, pread, pv, norm;
+  InstrWaits qk_in, qk_slot;     // qk's waits before its MFMAs (K block) and before its stores (S/P slot)
+  InstrWaits pread_pv;           // pread's and pv's waits (both about r_KV's step)
   InstrWaits acqk, acqv, acqs;   // acquire form: the drains at each tile (n = 0 in the linearized form)
   const int32_t *work;
   const __bf16 *q, *k, *v;
@@ -166,7 +183,8 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
   // SIMDs: their PREAD releases the S/P slot the next QK step needs (1 %
   // faster than equal priorities; raising the loaders or QK too was not)
   if (eng == 3) __builtin_amdgcn_s_setprio(2);
-  Sync<kMode, kInstr> S(P.sc, lds_addr(cnt), canon, wg);
+  constexpr bool kLean = kMode != BFS_MODE_BARRIER && !kInstr;
+  Sync<kMode, kInstr, kLean ? kSpinPolls : 0u> S(P.sc, lds_addr(cnt), canon, wg);
   const uint32_t own = S.word((uint32_t)eng, (uint32_t)ew);   // barrier mode: one counter per engine
 
   const size_t row_stride = (size_t)P.heads * kD;     // elements between tokens
@@ -202,7 +220,7 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
     return x;
   };
   Regs g;
-  Site<2> site;
+  LaneSite<2> site;
   Site<1> s_acq;                            // acquire form: the engine's wait at each tile
   uint64_t mark = 0;
 
@@ -249,6 +267,8 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
     uint32_t slot = 0;
     S.sync_point(own);                                       // before loop T
     S.enter(s_acq, acq, g, 1);
+    if (kLean) S.enter(site, iw, g, 2);
+    uint32_t last = 0;                                       // the previous tile's KV steps
     for (uint32_t t = 0; t < trip_t; ++t) {
       g.r1 += 1;
       g.h1 = t + 1;
@@ -260,7 +280,8 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
         S.signal(acq.update, 0);
       }
       S.sync_point(own);                                     // before loop KV
-      S.enter(site, iw, g, 2);
+      S.next_trip(site, iw, g, 2, last);
+      last = x.trip;
       for (uint32_t it = 0; it < x.trip; ++it, slot = (slot + 1 == depth) ? 0u : slot + 1) {
         g.r2 += 1;
         g.h2 = it + 1;
@@ -304,9 +325,16 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
   } else if (eng == 1) {
     // ---------------------------------------------------------- QK^T engine
     const uint32_t qr = 64u * ew;
+    LaneSite<2> s_slot;
     S.sync_point(own);                                       // before loop T
     S.enter(s_acq, P.acqs, g, 1);
-    uint32_t kslot = 0;
+    constexpr bool kSplit = kLean;
+    if (kLean) {
+      S.enter(site, P.qk_in, g, 2);
+      S.enter(s_slot, P.qk_slot, g, 2);
+    }
+    uint32_t last = 0;                                       // the previous tile's KV steps
+    uint32_t kslot = 0, row0 = pos16(l32, lhi);
     for (uint32_t t = 0; t < trip_t; ++t) {
       g.r1 += 1;
       g.h1 = t + 1;
@@ -327,11 +355,15 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
       S.wait(s_acq, P.acqs, g, t + 1, g.r1 - 1, [] {});   // ACQS
       S.signal(P.acqs.update, ew);
       S.sync_point(own);                                     // before loop KV
-      S.enter(site, P.qk, g, 2);
+      // Barrier-free: the MFMAs of a step run before its S/P slot is free; only
+      // the stores of S wait for it.
+      S.next_trip(site, kSplit ? P.qk_in : P.qk, g, 2, last);
+      if constexpr (kSplit) S.next_trip(s_slot, P.qk_slot, g, 2, last);
+      last = x.trip;
       for (uint32_t it = 0; it < x.trip; ++it, kslot = (kslot + 1 == (uint32_t)P.nk) ? 0u : kslot + 1) {
         g.r2 += 1;
         g.h2 = it + 1;
-        S.wait_affine(site, P.qk, g, it + 1, g.r2 - 1, [] {});
+        S.wait_affine(site, kSplit ? P.qk_in : P.qk, g, it + 1, g.r2 - 1, [] {});
         if (!S.aborted) {
           const uint32_t kb_base = kring + kslot * kKVSlot;
           const uint32_t sp = spbuf + ((g.r2 - 1) & 1u) * kSPSlot;
@@ -340,39 +372,41 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
           for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b) acc[a][b] = f32x16{};
-          // the K fragments of each 16-wide slice of d are read one slice
-          // ahead of the MFMAs that use them
-          bf16x8 k0 = lds_frag(kb_base + pos16(l32, lhi));
-          bf16x8 k1 = lds_frag(kb_base + pos16(32u + l32, lhi));
+          // K fragment f: slice f % 8 (16 of d) of key block f / 8.  Each is
+          // read kAhead - 1 fragments (64 cycles of MFMAs each) ahead of its
+          // use, and the first key block's S goes to LDS under the MFMAs of
+          // the second.
+          constexpr int kAhead = 4;
+          bf16x8 kf[kAhead];
+          // chunk 2 s + lhi of this lane's row is chunk lhi's offset XOR 32 s
+          // (one register instead of one for each of the 8 chunks)
+          auto k_frag = [&](int f) {
+            asm volatile("" : "+v"(row0));
+            return lds_frag(((kb_base + row0) ^ (32u * (f & 7))) + 32u * 256u * (f >> 3));
+          };
+          auto s_write = [&](int kb, int i) {
+            const int qb = i >> 2, j = i & 3;
+            const f32x4 v = {acc[qb][kb][4 * j], acc[qb][kb][4 * j + 1], acc[qb][kb][4 * j + 2],
+                             acc[qb][kb][4 * j + 3]};
+            asm volatile("" : "+v"(row0));
+            *(BFS_LDS f32x4 *)(uintptr_t)(((sp + 256u * qr + row0) ^ (128u * kb + 32u * j)) + 32u * 256u * qb) = v;
+          };
 #pragma unroll
-          for (int s = 0; s < 8; ++s) {
-            bf16x8 n0 = k0, n1 = k1;
-            if (s < 7) {
-              n0 = lds_frag(kb_base + pos16(l32, 2u * (s + 1) + lhi));
-              n1 = lds_frag(kb_base + pos16(32u + l32, 2u * (s + 1) + lhi));
-            }
+          for (int f = 0; f < kAhead; ++f) kf[f] = k_frag(f);
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-              acc[qb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0, qf[qb][s], acc[qb][0], 0, 0, 0);
-              acc[qb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1, qf[qb][s], acc[qb][1], 0, 0, 0);
-            }
-            if (s < 7) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-            k0 = n0;
-            k1 = n1;
+          for (int f = 0; f < 16; ++f) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+              acc[qb][f >> 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f % kAhead], qf[qb][f & 7], acc[qb][f >> 3], 0, 0, 0);
+            if (f + kAhead < 16) kf[f % kAhead] = k_frag(f + kAhead);
+            if (f > 8) s_write(0, f - 9);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kSplit)
+              if (f == 8) S.wait_affine(s_slot, P.qk_slot, g, it + 1, g.r2 - 1, [] {});
           }
+          s_write(0, 7);
 #pragma unroll
-          for (int qb = 0; qb < 2; ++qb) {
-            const uint32_t row = qr + 32u * qb + l32;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const f32x4 v = {acc[qb][kb][4 * j], acc[qb][kb][4 * j + 1], acc[qb][kb][4 * j + 2],
-                                 acc[qb][kb][4 * j + 3]};
-                *(BFS_LDS f32x4 *)(uintptr_t)(sp + pos16(row, 8u * kb + 2u * j + lhi)) = v;
-              }
-          }
+          for (int i = 0; i < 8; ++i) s_write(1, i);
         }
         S.signal(P.qk.update, (uint32_t)ew);
         S.sync_point(own);                                   // end of a KV iteration
@@ -384,13 +418,16 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
     const uint32_t row = 32u * ew + l32;
     const float c = P.scale_log2;
     S.sync_point(own);                                       // before loop T
+    if (kLean) S.enter(site, P.sm, g, 2);
+    uint32_t last = 0;                                       // the previous tile's KV steps
     for (uint32_t t = 0; t < trip_t; ++t) {
       g.r1 += 1;
       g.h1 = t + 1;
       const Tile x = tile(t);
       float m = -__builtin_inff(), lrun = 0.0f;
       S.sync_point(own);                                     // before loop KV
-      S.enter(site, P.sm, g, 2);
+      S.next_trip(site, P.sm, g, 2, last);
+      last = x.trip;
       for (uint32_t it = 0; it < x.trip; ++it) {
         g.r2 += 1;
         g.h2 = it + 1;
@@ -450,48 +487,61 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
     }
   } else {
     // --------------------------------------------------- PV engine and NORM
-    const uint32_t qr = 32u * ew;
+    // 64 query rows by 64 columns per wave (32 rows by 128 columns read every
+    // V fragment four times from LDS instead of twice)
+    const uint32_t qr = 64u * (ew >> 1), dcol = 64u * (ew & 1);
     // transposing V reads: lane l addresses row 8 (l / 32) + (l % 16) / 4 (+ 16 ks + 4 hh)
-    // and columns 32 db + 16 ((l / 16) % 2) + 4 (l % 4) .. + 3
+    // and columns dcol + 32 db + 16 ((l / 16) % 2) + 4 (l % 4) .. + 3
     const uint32_t xq = (lane >> 2) & 3u;
     const uint32_t vrow = 8u * lhi + xq;
-    uint32_t voff[4];
+    uint32_t voff[2];
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
-      voff[db] = vrow * 256u + 16u * (4u * ((uint32_t)db ^ xq) + 2u * ((lane >> 4) & 1u) + ((lane >> 1) & 1u)) +
+    for (int db = 0; db < 2; ++db)
+      voff[db] = vrow * 256u + 16u * (4u * ((dcol / 32u + (uint32_t)db) ^ xq) + 2u * ((lane >> 4) & 1u) + ((lane >> 1) & 1u)) +
                  8u * (lane & 1u);
-    Site<2> s_pr;
+    // Barrier-free: one poll for the waits of PREAD and of PV (the V block is
+    // loaded well before the step's P as a rule), so that the V fragments are
+    // read behind the P fragments without a second round trip.
+    constexpr bool kJoin = kLean;
+    LaneSite<kJoin ? 4 : 2> s_pr;
     Site<1> s_norm;
     uint32_t vslot = 0;
     S.sync_point(own);                                       // before loop T
     S.enter(s_norm, P.norm, g, 1);
+    if (kLean) S.enter(s_pr, P.pread_pv, g, 2);
+    uint32_t last = 0;                                       // the previous tile's KV steps
     for (uint32_t t = 0; t < trip_t; ++t) {
       g.r1 += 1;
       g.h1 = t + 1;
       const Tile x = tile(t);
-      f32x16 acc[4];
+      f32x16 acc[2][2];                                      // [query block][column block]
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[b] = f32x16{};
+      for (int b = 0; b < 4; ++b) acc[b >> 1][b & 1] = f32x16{};
       S.sync_point(own);                                     // before loop KV
-      S.enter(s_pr, P.pread, g, 2);
-      S.enter(site, P.pv, g, 2);
+      S.next_trip(s_pr, kJoin ? P.pread_pv : P.pread, g, 2, last);
+      if constexpr (!kJoin) S.next_trip(site, P.pv, g, 2, last);
+      last = x.trip;
       for (uint32_t it = 0; it < x.trip; ++it, vslot = (vslot + 1 == (uint32_t)P.nv) ? 0u : vslot + 1) {
         g.r2 += 1;
         g.h2 = it + 1;
         // PREAD: P and alpha of the step into registers, then the S/P slot
         // is released (LDS executes this wave's reads before its signal)
-        S.wait_affine(s_pr, P.pread, g, it + 1, g.r2 - 1, [] {});
-        bf16x8 pf[4];
-        float a = 1.0f;
+        S.wait_affine(s_pr, kJoin ? P.pread_pv : P.pread, g, it + 1, g.r2 - 1, [] {});
+        bf16x8 pf[2][4];
+        float a[2] = {1.0f, 1.0f};
         if (!S.aborted) {
           const uint32_t par = (g.r2 - 1) & 1u;
           const uint32_t sp = spbuf + par * kSPSlot;
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) pf[ks] = lds_frag(sp + pos16(qr + l32, 2u * (uint32_t)ks + lhi));
-          a = *(const BFS_LDS float *)(uintptr_t)(alpha_l + (par * kBQ + qr + l32) * 4u);
+          for (int qb = 0; qb < 2; ++qb)
+            a[qb] = *(const BFS_LDS float *)(uintptr_t)(alpha_l + (par * kBQ + qr + 32u * qb + l32) * 4u);
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) pf[qb][ks] = lds_frag(sp + pos16(qr + 32u * qb + l32, 2u * (uint32_t)ks + lhi));
         }
         S.signal(P.pread.update, (uint32_t)ew);
-        S.wait_affine(site, P.pv, g, it + 1, g.r2 - 1, [] {});
+        if constexpr (!kJoin) S.wait_affine(site, P.pv, g, it + 1, g.r2 - 1, [] {});
         if (!S.aborted) {
           const uint32_t vb = vring + vslot * kKVSlot;
           auto vfrag = [&](int ks, int db) {
@@ -499,27 +549,32 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
             const bf16x4 lo = lds_tr(va), hi = lds_tr(va + 4u * 256u);
             return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
           };
-          // the first V fragment is read before the rescale so that its
-          // latency overlaps it
-          bf16x8 vf = vfrag(0, 0);
-          // a block whose rows all keep their running maximum needs no rescale
-          if (__builtin_amdgcn_ballot_w64(a != 1.0f) != 0) {
+          // the V fragments of 16 keys are read two steps of 16 keys (256
+          // cycles of MFMAs) ahead of their use, the first before the rescale
+          bf16x8 vf[4][2];
 #pragma unroll
-            for (int db = 0; db < 4; ++db) acc[db] *= a;
-          }
-          // each V fragment is read one MFMA ahead of its use
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < 2; ++db) vf[ks][db] = vfrag(ks, db);
+          // a block whose rows all keep their running maximum needs no rescale
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb)
+            if (__builtin_amdgcn_ballot_w64(a[qb] != 1.0f) != 0) {
+              acc[qb][0] *= a[qb];
+              acc[qb][1] *= a[qb];
+            }
 #pragma unroll
           for (int ks = 0; ks < 4; ++ks) {
+            if (ks < 2) {
 #pragma unroll
-            for (int db = 0; db < 4; ++db) {
-              bf16x8 vf_next = vf;
-              if (db < 3) vf_next = vfrag(ks, db + 1);
-              else if (ks < 3) vf_next = vfrag(ks + 1, 0);
-              acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks], acc[db], 0, 0, 0);
-              if (db < 3 || ks < 3) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              vf = vf_next;
+              for (int db = 0; db < 2; ++db) vf[ks + 2][db] = vfrag(ks + 2, db);
             }
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+              for (int qb = 0; qb < 2; ++qb)
+                acc[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][db], pf[qb][ks], acc[qb][db], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
         S.signal(P.pv.update, (uint32_t)ew);
@@ -530,7 +585,9 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
       // softmax of the tile after next overwrite these row sums
       S.wait(s_norm, P.norm, g, t + 1, g.r1 - 1, [] {});
       if (!S.aborted) {
-        const uint32_t rloc = qr + l32;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+        const uint32_t rloc = qr + 32u * qb + l32;
         const int32_t row = x.q0 + (int32_t)rloc;
         const float lr = *(const BFS_LDS float *)(uintptr_t)(lsum_l + (((g.r1 - 1) & 1u) * kBQ + rloc) * 4u);
         const float inv = 1.0f / lr;
@@ -538,17 +595,17 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
         // block db: lanes l and l + 32 exchange halves (v_permlane32_swap) so
         // that the low lane holds the 8 columns of j = 0, 2 and the high lane
         // those of j = 1, 3, and each stores 16-byte row segments
-        __bf16 *dst = P.o + (size_t)(x.s0 + max(min(row, x.L - 1), 0)) * row_stride + (size_t)x.head * kD;
+        __bf16 *dst = P.o + (size_t)(x.s0 + max(min(row, x.L - 1), 0)) * row_stride + (size_t)x.head * kD + dcol;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < 2; ++db)
 #pragma unroll
           for (int jp = 0; jp < 2; ++jp) {
             uint32_t q[2][2];   // [j - 2 jp][dword]: this lane's 4 columns of j = 2 jp, 2 jp + 1
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
               const int j = 2 * jp + jj;
-              const f32x2 a01 = {acc[db][4 * j] * inv, acc[db][4 * j + 1] * inv};
-              const f32x2 a23 = {acc[db][4 * j + 2] * inv, acc[db][4 * j + 3] * inv};
+              const f32x2 a01 = {acc[qb][db][4 * j] * inv, acc[qb][db][4 * j + 1] * inv};
+              const f32x2 a23 = {acc[qb][db][4 * j + 2] * inv, acc[qb][db][4 * j + 3] * inv};
               q[jj][0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a01, bf16x2));
               q[jj][1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a23, bf16x2));
             }
@@ -569,6 +626,7 @@ __global__ void __launch_bounds__(768) attn_kernel(AttnParams P) {
             const int j = 2 * jp + (int)lhi;
             if (row < x.L) *reinterpret_cast<u32x4 *>(dst + 32 * db + 8 * j) = v;
           }
+      }
       }
       S.signal(P.norm.update, (uint32_t)ew);
       S.sync_point(own);                                     // end of a T iteration
@@ -664,6 +722,16 @@ bfs_status launch_attn(const bfs_plan *p, DevImage *img, const void *const *bufs
       (!no_dynamic(P.loadk) || !no_dynamic(P.loadv) || !no_dynamic(P.qk) || !no_dynamic(P.sm) ||
        !no_dynamic(P.pread) || !no_dynamic(P.pv)))
     return fail(BFS_E_UNSUPPORTED, "attn: a KV-loop wait depends on a loop register other than the KV loop's");
+  // QK's waits by what they protect
+  P.qk_in = P.qk_slot = P.qk;
+  P.qk_in.n = P.qk_slot.n = 0;
+  for (int j = 0; j < P.qk.n; ++j) {
+    const uint32_t dep = P.qk.w[j].w.w3 & 0xffffu;
+    InstrWaits &to = p->deps[3 * dep] == pr ? P.qk_slot : P.qk_in;
+    to.w[to.n++] = P.qk.w[j];
+  }
+  P.pread_pv = P.pread;
+  for (int j = 0; j < P.pv.n && P.pread_pv.n < kMaxWaits; ++j) P.pread_pv.w[P.pread_pv.n++] = P.pv.w[j];
   P.sc = sync_common(img, dbg, dbg_cap, o, kWaves);
   P.work = static_cast<const int32_t *>(bufs[0]);
   P.q = static_cast<const __bf16 *>(bufs[1]);
