@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import numpy as np
 
@@ -126,10 +127,46 @@ def _ptr(x):
     return x.data_ptr()
 
 
+_torch_C = None          # torch's binding module, once a device is in use
+
+
+def _ptr_array(buffers):
+    """The buffers' addresses as a C array (packed bytes: a fifth of the time
+    of a ctypes array)."""
+    return struct.pack("%dP" % len(buffers), *[b if isinstance(b, int) else 0 if b is None else b.data_ptr() for b in buffers])
+
+
+# The options of a run that names none, shared by all such runs (the library
+# only reads them).  They are told by identity with the defaults: any other
+# value, of whatever type, is converted and checked by ctypes.
+_NO_OPTS = RunOpts(0, -1, 0, None, 0, 0)
+_ZERO, _NO_DEP = 0, -1
+
+
+def _run_opts(watchdog_polls, fault_dep, fault_delta, stats, k_unroll, flags):
+    if (stats is None and fault_dep is _NO_DEP and watchdog_polls is _ZERO and fault_delta is _ZERO
+            and k_unroll is _ZERO and flags is _ZERO):
+        return C.byref(_NO_OPTS)
+    return C.byref(RunOpts(watchdog_polls, fault_dep, fault_delta, _ptr(stats), k_unroll, flags))
+
+
+_torch = None             # torch, once its device bindings were found
+
+
 def _stream_handle(stream):
+    """Stream handle of an int or torch stream; None: torch's current stream
+    of the current device, read through the bindings that
+    torch.cuda.current_stream() wraps (the stream object around the handle
+    takes most of its 2.6 us)."""
+    global _torch
     if stream is None:
+        if _torch is not None and _torch.cuda.is_initialized():       # (not so in a forked child)
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        handle = torch.cuda.current_stream().cuda_stream              # initializes the device, or raises
+        if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+            _torch = torch
+        return handle
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -209,19 +246,20 @@ class Plan:
         stats: optional int64 tensor of n_wg * n_waves * 8 per-wave counters;
         k_unroll: K-loop unroll factor of GEMM launches (0, 1, 2, 4, 8);
         flags: RUN_PER_INSTANCE / RUN_LOG_BATCHED (stream family)."""
-        arr = (C.c_void_p * max(1, len(buffers)))(*[_ptr(b) for b in buffers])
-        opts = RunOpts(watchdog_polls, fault_dep, fault_delta, _ptr(stats), k_unroll, flags)
-        _check(lib().bfs_run(self.handle, arr, len(buffers), _ptr(trips), _ptr(trip_off), n_wg,
-                             _stream_handle(stream), _ptr(debug_log), debug_capacity, C.byref(opts)))
+        L = _lib or lib()
+        st = L.bfs_run(self.handle, _ptr_array(buffers), len(buffers), _ptr(trips), _ptr(trip_off), n_wg,
+                       _stream_handle(stream), _ptr(debug_log), debug_capacity,
+                       _run_opts(watchdog_polls, fault_dep, fault_delta, stats, k_unroll, flags))
+        if st != OK:
+            _check(st)
 
     def run_noalloc(self, buffers, trips, trip_off, n_wg, stream=None, debug_log=None, debug_capacity=0,
                     watchdog_polls=0, fault_dep=-1, fault_delta=0, stats=None, k_unroll=0, flags=0):
         """As run(), through bfs_run_noalloc: the plan's tables and error words
         live in the library's fixed device array instead of an allocation."""
-        arr = (C.c_void_p * max(1, len(buffers)))(*[_ptr(b) for b in buffers])
-        opts = RunOpts(watchdog_polls, fault_dep, fault_delta, _ptr(stats), k_unroll, flags)
-        _check(lib().bfs_run_noalloc(self.handle, arr, len(buffers), _ptr(trips), _ptr(trip_off), n_wg,
-                                     _stream_handle(stream), _ptr(debug_log), debug_capacity, C.byref(opts)))
+        _check(lib().bfs_run_noalloc(self.handle, _ptr_array(buffers), len(buffers), _ptr(trips), _ptr(trip_off), n_wg,
+                                     _stream_handle(stream), _ptr(debug_log), debug_capacity,
+                                     _run_opts(watchdog_polls, fault_dep, fault_delta, stats, k_unroll, flags)))
 
     def status(self, stream=None):
         """Synchronize the stream; raise BfsError(E_DEADLOCK) if a wait gave up."""
