@@ -89,6 +89,14 @@ __device__ __forceinline__ void retire_all_and_add(uint32_t addr, uint32_t n) {
 
 __device__ __forceinline__ void drain_all() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
+// Barrier of the workgroup after its LDS writes; loads stay in flight
+// (__syncthreads() waits for them too).
+__device__ __forceinline__ void sync_lds() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Counted wait on vector-memory operations (direct-to-LDS loads complete in
 // issue order): at most N may remain outstanding.
 template <int N>

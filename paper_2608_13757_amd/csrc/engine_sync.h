@@ -404,30 +404,17 @@ struct Sync {
     }
   }
 
-  // The words of a LaneSite as they are now, for a later wait_affine: counters
-  // only grow, so a threshold they reach stays reached, and the read is in
-  // flight while the wave does something else.
-  template <int kN>
-  __device__ __forceinline__ uint32_t peek(const LaneSite<kN> &s) const {
-    if constexpr (kMode == BFS_MODE_BARRIER || kInstr) return 0u;
-    return *(volatile BFS_LDS uint32_t *)(uintptr_t)s.addr;
-  }
-
   // wait_affine on a LaneSite: kSpin polls of a blocked wait, then the
-  // general wait with its sleeps and watchdog.  seen: words from peek().
+  // general wait with its sleeps and watchdog.
   template <int kN, class OnBlock>
   __device__ __forceinline__ void wait_affine(LaneSite<kN> &s, const InstrWaits &iw, const Regs &g, uint32_t t,
-                                              uint32_t instance, OnBlock on_block, uint32_t seen = 0) {
+                                              uint32_t instance, OnBlock on_block) {
     if constexpr (kMode == BFS_MODE_BARRIER || kInstr) {
       wait(s.site, iw, g, t, instance, on_block);
     } else {
       if (aborted) return;
       const int32_t v = s.base + (int32_t)((s.mk >> 16) * t);
       const uint32_t thr = (t > (s.mk & 0xffffu) && v > 0) ? (uint32_t)v : 0u;
-      if (__ballot(seen < thr) == 0ull) {
-        asm volatile("" ::: "memory");     // (no access of the instruction before the test)
-        return;
-      }
       for (uint32_t polls = 0; polls <= kSpin; ++polls) {
         if (__ballot(lds_poll(s.addr) < thr) == 0ull) return;
         on_block();
