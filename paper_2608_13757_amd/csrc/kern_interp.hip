@@ -27,10 +27,18 @@
 //     every barrier.  Instrumented launches retire each instruction at once.
 //   * a wait already met by the last observed counter value (counters only
 //     grow, barrier mode aside) is not polled again.
+//   * an innermost loop of one instruction with at most two waits (the usual
+//     one: an engine's projection holds its own instructions only) is decoded
+//     once and run without the dispatch, which is some 300 scalar instructions
+//     per iteration and trip on the general path and 40 here: thresholds, slots
+//     and tiles are carried incrementally, trips are read 64 at a time, and
+//     where the loop around it holds nothing else the trips follow one another.
 // The ring program (64 outer iterations, 4 slots, 1024 workgroups, 303 MB of
-// tiles) takes 496 us against 1705 us with tables, loop registers and
-// execution counts read from memory and LDS and every instruction drained
-// before the next.
+// tiles) takes 164 us, 492 us with every instruction dispatched, and 1705 us
+// with tables, loop registers and execution counts read from memory and LDS and
+// every instruction drained before the next.
+#include <type_traits>
+
 #include "bfs_internal.h"
 #include "device_sync.h"
 
@@ -42,6 +50,18 @@ constexpr int kMaxInstrsInterp = 256;
 constexpr uint32_t kMaxPending = 8;     // vector-memory instructions in flight per engine
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// One of an inner loop's waits, decoded, and its state in a run of trips: the
+// threshold is run, growing by N with r of loop P, while rhat of loop S > kk.
+// (Members by name: arrays, even with unrolled indexes, went to scratch memory.)
+struct InnerWait {
+  uint32_t addr = 0, dep = 0, k = 0, lP = 0, lS = 0, mask = 0;
+  int32_t N = 0, c = 0;
+};
+struct InnerWaitState {
+  int32_t run, step, step_a;
+  uint32_t kk, met;
+};
 
 struct InterpParams {
   const int32_t *code;          // code words, 4 x int32
@@ -134,9 +154,9 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) wr[j] = (uint32_t)P.waits[8 * (wait0 + lane) + j];
   }
-  auto code = [&](uint32_t pc, int j) { return kLanes ? rl(cw[j], pc) : (uint32_t)ldc(P.code + 4 * (code0 + pc) + j); };
-  auto arg = [&](uint32_t row, int j) { return kLanes ? rl(ar[j], row) : (uint32_t)ldc(P.args + 8 * (row0 + row) + j); };
-  auto wrow = [&](uint32_t w, int j) { return kLanes ? rl(wr[j], w) : (uint32_t)ldc(P.waits + 8 * (wait0 + w) + j); };
+  auto code = [&](uint32_t pc, int j) __attribute__((always_inline)) { return kLanes ? rl(cw[j], pc) : (uint32_t)ldc(P.code + 4 * (code0 + pc) + j); };
+  auto arg = [&](uint32_t row, int j) __attribute__((always_inline)) { return kLanes ? rl(ar[j], row) : (uint32_t)ldc(P.args + 8 * (row0 + row) + j); };
+  auto wrow = [&](uint32_t w, int j) __attribute__((always_inline)) { return kLanes ? rl(wr[j], w) : (uint32_t)ldc(P.waits + 8 * (wait0 + w) + j); };
   // Loop registers and trip-table offsets, loop l in lane l (at most 32).
   uint32_t rv = lane == 0 ? 1u : 0u, hv = rv, tv = rv;
   uint32_t off_lo = 0, off_hi = 0;
@@ -168,7 +188,7 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
 
   const uint32_t snap = lds_addr(snap_p);
   const uint32_t cnt_base = lds_addr(cnt), data_l = lds_addr(data);
-  auto counter = [&](uint32_t slot) { return cnt_base + 4u * slot * (uint32_t)bfs::kMaxWavesPerEngine; };
+  auto counter = [&](uint32_t slot) __attribute__((always_inline)) { return cnt_base + 4u * slot * (uint32_t)bfs::kMaxWavesPerEngine; };
   const uint32_t own_words = counter(e);
   uint32_t *log_entries = nullptr;
   uint32_t nlog = 0;
@@ -193,34 +213,34 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
   // change of it empties the queue first.
   uint64_t queue = 0;
   uint32_t pending = 0, ops = 1;
-  auto add_slot = [&](uint32_t slot1) {
+  auto add_slot = [&](uint32_t slot1) __attribute__((always_inline)) {
     if (slot1 != 0u) lds_add(counter(slot1 - 1u), 1u);
   };
-  auto retire_one = [&]() {
+  auto retire_one = [&]() __attribute__((always_inline)) {
     pending -= 1;
     wait_at_most(pending * ops);
     add_slot((uint32_t)queue & 0xffu);
     queue >>= 8;
   };
-  auto retire_all = [&]() {
+  auto retire_all = [&]() __attribute__((always_inline)) {
     if (pending > 0) {
       wait_vm<0>();
       for (; pending > 0; --pending, queue >>= 8) add_slot((uint32_t)queue & 0xffu);
     }
   };
-  auto issued = [&](uint32_t slot1) {      // one more instruction of `ops` accesses is in flight
+  auto issued = [&](uint32_t slot1) __attribute__((always_inline)) {      // one more instruction of `ops` accesses is in flight
     queue |= (uint64_t)slot1 << (8u * pending);
     pending += 1;
     if (kInstr) retire_all();
     else if (pending == kMaxPending || (pending + 1u) * ops > 16u) retire_one();
   };
-  auto want_ops = [&](uint32_t n) {
+  auto want_ops = [&](uint32_t n) __attribute__((always_inline)) {
     if (ops != n) {
       retire_all();
       ops = n;
     }
   };
-  auto barrier_point = [&]() {             // Section 3.4: drain, meet, reset, meet
+  auto barrier_point = [&]() __attribute__((always_inline)) {             // Section 3.4: drain, meet, reset, meet
     retire_all();
     const uint64_t t0 = (kInstr && stt.on) ? now_ticks() : 0;
     region_sync(own_words, 1);
@@ -228,7 +248,7 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
     seen = 0;                              // the counters were reset
   };
   // Poll until the counter reaches thr, retiring what this engine holds.
-  auto poll_until = [&](uint32_t addr, uint32_t thr, uint32_t dep, uint32_t inst) -> uint32_t {
+  auto poll_until = [&](uint32_t addr, uint32_t thr, uint32_t dep, uint32_t inst) __attribute__((always_inline)) -> uint32_t {
     uint32_t polls = 0;
     while (true) {
       const uint32_t v = uniform(lds_poll(addr));
@@ -242,14 +262,261 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
         aborted = 1u;
         return v;
       }
-      __builtin_amdgcn_s_sleep(1);
+      if (polls > 16u) __builtin_amdgcn_s_sleep(1);
     }
+  };
+
+  // Datapath pieces shared by the general path and the inner loop.
+  auto ring_at = [&](uint32_t id) __attribute__((always_inline)) {        // 0 .. 3, selected without indexing (stays in scalar registers)
+    return (uint32_t)(id == 0 ? P.ring_off[0] : id == 1 ? P.ring_off[1] : id == 2 ? P.ring_off[2] : P.ring_off[3]);
+  };
+  auto load_tile = [&](uint32_t dst, const float *src) __attribute__((always_inline)) {
+    want_ops(ld_ops);
+    if (P.wide_x) {
+      __builtin_amdgcn_global_load_lds((const void *)(src + 4 * lane), (BFS_LDS void *)(uintptr_t)dst, 16, 0, 0);
+    } else {
+      for (uint32_t i = 0; i < T; i += 64u)
+        __builtin_amdgcn_global_load_lds((const void *)(src + i + lane), (BFS_LDS void *)(uintptr_t)(dst + 4u * i), 4, 0, 0);
+    }
+  };
+  // writes one tile to HBM as st_ops stores, in flight
+  auto store_tile = [&](uint32_t src, float *dst) __attribute__((always_inline)) {
+    want_ops(st_ops);
+    if (P.wide_out) {
+      *reinterpret_cast<f32x4 *>(dst + 4 * lane) = *(const BFS_LDS f32x4 *)(uintptr_t)(src + 16u * lane);
+    } else {
+      for (uint32_t i = 0; i < T; i += 64u) dst[i + lane] = *(const BFS_LDS float *)(uintptr_t)(src + 4u * (i + lane));
+    }
+  };
+  auto scale_acc = [&](uint32_t acc, uint32_t src, float c) __attribute__((always_inline)) {         // acc += c * slot
+    if (T == 256u) {
+      BFS_LDS f32x4 *a = (BFS_LDS f32x4 *)(uintptr_t)(acc + 16u * lane);
+      f32x4 v = *a;
+      const f32x4 x = *(const BFS_LDS f32x4 *)(uintptr_t)(src + 16u * lane);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = v[j] + c * x[j];
+      *a = v;
+    } else {
+      for (uint32_t i = lane; i < T; i += 64u) {
+        BFS_LDS float *a = (BFS_LDS float *)(uintptr_t)(acc + 4u * i);
+        *a = *a + c * *(const BFS_LDS float *)(uintptr_t)(src + 4u * i);
+      }
+    }
+  };
+  auto add_const = [&](uint32_t dst, uint32_t src, float c) __attribute__((always_inline)) {         // slot + c
+    for (uint32_t i = lane; i < T; i += 64u)
+      *(BFS_LDS float *)(uintptr_t)(dst + 4u * i) = *(const BFS_LDS float *)(uintptr_t)(src + 4u * i) + c;
+  };
+
+  // Trips of one loop, read 64 at a time: lane i holds entry tw_first + i of
+  // the trip list of loop tw_loop.  next_trip: entry i of loop l, of which
+  // `left` more follow for sure (those of its parent's remaining iterations);
+  // called with nothing in flight where it has to read.
+  uint32_t tw = 0, tw_loop = ~0u, tw_first = 0, tw_n = 0;
+  auto has_trip = [&](uint32_t l, uint32_t i) __attribute__((always_inline)) { return l == tw_loop && i - tw_first < tw_n; };
+  auto read_trips = [&](uint32_t l, uint32_t i, uint32_t left) __attribute__((always_inline)) {
+    const int64_t o = (int64_t)((uint64_t)rl(off_lo, l) | (uint64_t)rl(off_hi, l) << 32);
+    tw_loop = l;
+    tw_first = i;
+    tw_n = min(left, 63u) + 1u;
+    if (lane < tw_n) tw = (uint32_t)P.trips[o + (int64_t)i + lane];
+    asm volatile("" : "+v"(tw));           // waited for here
+  };
+
+  // The last inner loop found at an instruction, decoded (see below).
+  struct Inner {
+    uint32_t pc = ~0u;                     // the instruction it was decoded from
+    bool ok = false, nest = false;
+    uint32_t l = 0, a = 0, op = 0, slot1 = 0, wait = 0, n_waits = 0;
+    InnerWait w0, w1;
+    int32_t a2 = 0, a4 = 0;
+    uint32_t a3 = 0, a5 = 0, a6 = 0, src = 0, dst = 0;
+    float k_const = 0.f;
+  } F;
+  // Runs the decoded loop from its first iteration of a trip on; returns the
+  // code words it passes.
+  enum { LOAD_WIDE, SCALE_256, OTHER };
+  auto run_inner = [&](auto which) __attribute__((always_inline)) -> uint32_t {
+    constexpr int kWhich = decltype(which)::value;
+    const bool tiles = kWhich == LOAD_WIDE || (kWhich == OTHER && (F.op == 1u || F.op == 5u));
+    const uint32_t l = F.l, a = F.a, own = counter(F.slot1 - 1u);
+    uint32_t r = rl(rv, l), n = rl(tv, l);               // r of the trip's first iteration
+    uint32_t ra = rl(rv, a), ha = rl(hv, a);
+    const uint32_t ta = F.nest ? rl(tv, a) : ha;
+    // what is in flight is this instruction's, so that the queue is a count
+    // (a sum: a choice between captured variables would keep all of them in
+    // scratch memory)
+    const uint32_t is_ld = F.op == 1u, is_st = F.op == 5u;
+    const uint32_t n_ops = is_ld * ld_ops + is_st * st_ops + (1u - is_ld - is_st) * ops;
+    const uint64_t same = (uint64_t)F.slot1 * 0x0101010101010101ull;
+    if (pending > 0 && (ops != n_ops || !tiles || queue != (same & ((1ull << (8u * (pending & 7u))) - 1ull)))) retire_all();
+    ops = n_ops;
+    const uint32_t most = max(min(kMaxPending, 16u / ops), 1u) - 1u;   // in flight after an instruction
+    auto signal = [&](uint32_t m) __attribute__((always_inline)) {
+      if (F.slot1 != 0u) lds_add(own, m);
+    };
+    auto start = [&](const InnerWait &w, uint32_t row) __attribute__((always_inline)) {
+      InnerWaitState x;
+      x.run = w.N * (int32_t)rl(rv, w.lP) - w.c;
+      x.step = w.lP == l ? w.N : 0;
+      x.step_a = w.lP == a ? w.N : 0;
+      x.kk = !w.mask ? 0u : w.lS == l ? w.k : (rl(hv, w.lS) > w.k ? 0u : ~0u);
+      x.met = row < 64u ? rl(seen, row & 63u) : 0u;
+      return x;
+    };
+    InnerWaitState x0 = start(F.w0, F.wait), x1 = start(F.w1, F.wait + 1u);
+    auto wait = [&](const InnerWait &w, InnerWaitState &x, uint32_t h) __attribute__((always_inline)) {
+      if (x.run > (int32_t)x.met && h > x.kk && !aborted) {
+        uint32_t polls = 0;
+        while (true) {
+          x.met = uniform(lds_poll(w.addr));
+          if ((int32_t)x.met >= x.run) break;
+          if (pending > 0) {
+            pending -= 1;
+            wait_at_most(pending * ops);
+            signal(1u);
+          } else if (++polls > limit) {
+            report_deadlock(P.err, w.dep, (uint32_t)wg, r - 1u, (uint32_t)x.run, x.met, (uint32_t)wave);
+            aborted = 1u;
+            break;
+          } else if (polls > 16u) {
+            __builtin_amdgcn_s_sleep(1);
+          }
+        }
+      }
+      x.run += x.step;
+    };
+    // slot and tile
+    const bool p4 = F.a4 >= 0, p2 = F.a2 >= 0;
+    uint32_t s4 = p4 ? umod(rl(hv, (uint32_t)F.a4) - 1u, F.a5) : 0u;
+    uint32_t s2 = p2 ? umod(rl(rv, (uint32_t)F.a2) - 1u, F.a3) : 0u;
+    const uint32_t mul2 = p2 ? F.a5 : 0u;
+    const uint32_t d4 = F.a4 == (int32_t)l ? 1u : 0u, d2 = F.a2 == (int32_t)l ? 1u : 0u;
+    int64_t tile = tiles ? (tbase + (int64_t)rl(rv, F.a6) - 1) * (int64_t)T : 0;
+    const int64_t d6 = tiles && F.a6 == l ? (int64_t)T : 0;
+    while (true) {
+      for (uint32_t h = 1; h <= n; ++h, ++r) {
+        wait(F.w0, x0, h);
+        wait(F.w1, x1, h);
+        const uint32_t slot = 4u * T * (s4 + s2 * mul2);
+        if (tiles && !aborted) {
+          if (kWhich == LOAD_WIDE)
+            __builtin_amdgcn_global_load_lds((const void *)(P.x + tile + 4 * lane), (BFS_LDS void *)(uintptr_t)(F.dst + slot), 16, 0, 0);
+          else if (F.op == 1u)
+            load_tile(F.dst + slot, P.x + tile);
+          else
+            store_tile(F.src + slot, P.out + tile);
+          if (pending >= most) {
+            if (kWhich == LOAD_WIDE) wait_vm<kMaxPending - 1>(); else wait_at_most(pending * ops);
+            signal(1u);
+          } else {
+            pending += 1;
+          }
+        } else {
+          if (!aborted) {
+            if (kWhich == SCALE_256 || F.op == 2u) scale_acc(F.dst, F.src + slot, F.k_const);
+            else add_const(F.dst + slot, F.src + slot, F.k_const);
+          }
+          signal(1u);
+        }
+        s4 = s4 + d4 == F.a5 ? 0u : s4 + d4;
+        s2 = s2 + d2 == F.a3 ? 0u : s2 + d2;
+        tile += d6;
+      }
+      if (ha == ta) break;
+      // the next iteration of the loop around it, which holds nothing else
+      ra += 1u;
+      ha += 1u;
+      if (!has_trip(l, ra - 1u)) {
+        if (pending > 0) {
+          wait_vm<0>();
+          signal(pending);
+          pending = 0;
+        }
+        read_trips(l, ra - 1u, ta - ha);
+      }
+      n = rl(tw, ra - 1u - tw_first);
+      x0.run += x0.step_a;
+      x1.run += x1.step_a;
+      if (F.w0.mask && F.w0.lS == a) x0.kk = ha > F.w0.k ? 0u : ~0u;
+      if (F.w1.mask && F.w1.lS == a) x1.kk = ha > F.w1.k ? 0u : ~0u;
+      if (d4) s4 = 0u;
+      if (F.a4 == (int32_t)a) s4 = s4 + 1u == F.a5 ? 0u : s4 + 1u;
+      if (F.a2 == (int32_t)a) s2 = s2 + 1u == F.a3 ? 0u : s2 + 1u;
+      if (tiles && F.a6 == a) tile += (int64_t)T;
+    }
+    if (F.n_waits > 0u && F.wait < 64u) seen = wl(seen, F.wait, x0.met);
+    if (F.n_waits > 1u && F.wait + 1u < 64u) seen = wl(seen, F.wait + 1u, x1.met);
+    queue = pending > 0 ? same & ((1ull << (8u * pending)) - 1ull) : 0ull;
+    rv = wl(rv, l, r - 1u);
+    hv = wl(hv, l, n);
+    tv = wl(tv, l, n);
+    if (!F.nest) return 2u;
+    rv = wl(rv, a, ra);
+    hv = wl(hv, a, ha);
+    return 3u;
   };
 
   uint32_t pc = 0;
   while (true) {
     const uint32_t w0 = code(pc, 0), kind = w0 & 0xffu;
     const uint32_t w1 = code(pc, 1), w2 = code(pc, 2), w3 = code(pc, 3);
+    // A loop of one instruction with at most two waits (the usual innermost
+    // loop of an engine): all that the general path below decodes for each
+    // instruction and loop end is decoded once for the loop and evaluated once
+    // per trip, and the iterations of a trip follow one another.
+    if (kMode == BFS_MODE_BARRIER_FREE && !kInstr && kind == bfs::CODE_INSTR && !aborted) {
+      if (pc != F.pc) {
+        F.pc = pc;
+        F.op = (w0 >> 8) & 0xffu;
+        F.slot1 = w0 >> 24;
+        F.wait = w2;
+        F.n_waits = w3;
+        F.l = code(pc + 1, 1);
+        // the loop around it, if it holds nothing but this loop
+        const uint32_t e0 = code(pc + 2, 0);
+        F.a = pc > 0u ? code(pc - 1u, 3) : 0u;
+        F.nest = (e0 & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 2, 1) == F.a && code(pc + 2, 2) + 2u == pc &&
+                 ((P.fallback_loops >> F.a) & 1u) == 0u;
+        F.ok = (code(pc + 1, 0) & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 1, 2) + 1u == pc &&
+               ((P.fallback_loops >> F.l) & 1u) == 0u && w3 <= 2u && (F.op == 1u || F.op == 2u || F.op == 4u || F.op == 5u);
+        auto decode = [&](uint32_t j) __attribute__((always_inline)) {
+          InnerWait x;
+          if (F.ok && j < w3) {
+            const uint32_t q0 = wrow(w2 + j, 0);
+            x.addr = counter(q0 & 0xffu);
+            x.dep = wrow(w2 + j, 1);
+            x.k = wrow(w2 + j, 2);
+            x.lP = (q0 >> 8) & 0xffu;
+            x.lS = (q0 >> 16) & 0xffu;
+            x.mask = (q0 >> 24) & 1u;
+            x.N = (int32_t)wrow(w2 + j, 4);
+            x.c = x.N * (int32_t)wrow(w2 + j, 3) + (x.N - (int32_t)wrow(w2 + j, 5));
+            F.ok = F.ok && wrow(w2 + j, 6) == 0u;            // (no snapshots)
+          }
+          return x;
+        };
+        F.w0 = decode(0u);
+        F.w1 = decode(1u);
+        if (F.ok) {
+          F.a2 = (int32_t)arg(w1, 2);
+          F.a3 = arg(w1, 3);
+          F.a4 = (int32_t)arg(w1, 4);
+          F.a5 = arg(w1, 5);
+          F.a6 = arg(w1, 6);
+          F.k_const = __uint_as_float(arg(w1, 7));
+          const uint32_t a0 = arg(w1, 0), a1 = arg(w1, 1);
+          F.src = data_l + 4u * ring_at(a0);
+          F.dst = data_l + 4u * (F.op == 2u ? (uint32_t)P.acc_off + a1 * T : ring_at(a1));
+        }
+      }
+      if (F.ok && rl(hv, F.l) == 1u) {
+        if (F.op == 1u && P.wide_x) pc += run_inner(std::integral_constant<int, LOAD_WIDE>{});
+        else if (F.op == 2u && T == 256u) pc += run_inner(std::integral_constant<int, SCALE_256>{});
+        else pc += run_inner(std::integral_constant<int, OTHER>{});
+        continue;
+      }
+    }
     if (__builtin_expect(kind == bfs::CODE_INSTR, 1)) {
       // CODE_INSTR: w0 = kind | opcode << 8 | innermost loop << 16 | (counter
       // slot + 1) << 24, w1 its row, w2 its first wait row, w3 its waits.  The
@@ -293,36 +560,15 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
       bool in_flight = false;                // retires later, in order
       if (!aborted && op != 0u) {
         // ring slot and tile index
-        auto slot_of = [&]() {
+        auto slot_of = [&]() __attribute__((always_inline)) {
           const int32_t a2 = (int32_t)arg(w1, 2), a4 = (int32_t)arg(w1, 4);
           uint32_t s = a4 >= 0 ? umod(rl(hv, (uint32_t)a4) - 1u, arg(w1, 5)) : 0u;
           if (a2 >= 0) s += umod(rl(rv, (uint32_t)a2) - 1u, arg(w1, 3)) * arg(w1, 5);
           return s;
         };
-        auto ring_at = [&](uint32_t id) {    // 0 .. 3, selected without indexing (stays in scalar registers)
-          return (uint32_t)(id == 0 ? P.ring_off[0] : id == 1 ? P.ring_off[1] : id == 2 ? P.ring_off[2] : P.ring_off[3]);
-        };
-        auto tile_of = [&]() { return (tbase + (int64_t)rl(rv, arg(w1, 6)) - 1) * (int64_t)T; };
-        // writes the registers of one tile to HBM as st_ops stores, in flight
-        auto store_tile = [&](uint32_t src, float *dst) {
-          want_ops(st_ops);
-          if (P.wide_out) {
-            *reinterpret_cast<f32x4 *>(dst + 4 * lane) = *(const BFS_LDS f32x4 *)(uintptr_t)(src + 16u * lane);
-          } else {
-            for (uint32_t i = 0; i < T; i += 64u) dst[i + lane] = *(const BFS_LDS float *)(uintptr_t)(src + 4u * (i + lane));
-          }
-          in_flight = true;
-        };
+        auto tile_of = [&]() __attribute__((always_inline)) { return (tbase + (int64_t)rl(rv, arg(w1, 6)) - 1) * (int64_t)T; };
         if (op == 1u) {          // load
-          want_ops(ld_ops);
-          const float *src = P.x + tile_of();
-          const uint32_t dst = data_l + 4u * (ring_at(arg(w1, 1)) + slot_of() * T);
-          if (P.wide_x) {
-            __builtin_amdgcn_global_load_lds((const void *)(src + 4 * lane), (BFS_LDS void *)(uintptr_t)dst, 16, 0, 0);
-          } else {
-            for (uint32_t i = 0; i < T; i += 64u)
-              __builtin_amdgcn_global_load_lds((const void *)(src + i + lane), (BFS_LDS void *)(uintptr_t)(dst + 4u * i), 4, 0, 0);
-          }
+          load_tile(data_l + 4u * (ring_at(arg(w1, 1)) + slot_of() * T), P.x + tile_of());
           in_flight = true;
         } else {
           // the engine's earlier loads have landed before it reads a slot, and
@@ -330,30 +576,17 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
           retire_all();
           const float c = __uint_as_float(arg(w1, 7));
           if (op == 2u) {        // acc += c * slot
-            const uint32_t src = data_l + 4u * (ring_at(arg(w1, 0)) + slot_of() * T);
-            const uint32_t acc = data_l + 4u * ((uint32_t)P.acc_off + arg(w1, 1) * T);
-            if (T == 256u) {
-              BFS_LDS f32x4 *a = (BFS_LDS f32x4 *)(uintptr_t)(acc + 16u * lane);
-              f32x4 v = *a;
-              const f32x4 s = *(const BFS_LDS f32x4 *)(uintptr_t)(src + 16u * lane);
-  #pragma unroll
-              for (int j = 0; j < 4; ++j) v[j] = v[j] + c * s[j];
-              *a = v;
-            } else {
-              for (uint32_t i = lane; i < T; i += 64u) {
-                BFS_LDS float *a = (BFS_LDS float *)(uintptr_t)(acc + 4u * i);
-                *a = *a + c * *(const BFS_LDS float *)(uintptr_t)(src + 4u * i);
-              }
-            }
+            scale_acc(data_l + 4u * ((uint32_t)P.acc_off + arg(w1, 1) * T),
+                      data_l + 4u * (ring_at(arg(w1, 0)) + slot_of() * T), c);
           } else if (op == 3u) { // store acc
             store_tile(data_l + 4u * ((uint32_t)P.acc_off + arg(w1, 0) * T), P.out + (int64_t)wg * T);
+            in_flight = true;
           } else if (op == 4u) { // slot + c
             const uint32_t s = slot_of() * T;
-            const uint32_t src = data_l + 4u * (ring_at(arg(w1, 0)) + s), dst = data_l + 4u * (ring_at(arg(w1, 1)) + s);
-            for (uint32_t i = lane; i < T; i += 64u)
-              *(BFS_LDS float *)(uintptr_t)(dst + 4u * i) = *(const BFS_LDS float *)(uintptr_t)(src + 4u * i) + c;
+            add_const(data_l + 4u * (ring_at(arg(w1, 1)) + s), data_l + 4u * (ring_at(arg(w1, 0)) + s), c);
           } else if (op == 5u) { // store slot
             store_tile(data_l + 4u * (ring_at(arg(w1, 0)) + slot_of() * T), P.out + tile_of());
+            in_flight = true;
           }
         }
       }
@@ -394,8 +627,13 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
     if (kind == bfs::CODE_LOOP) {          // w1 loop, w2 its end word, w3 parent
       if (kMode == BFS_MODE_BARRIER) barrier_point();
       const uint32_t l = w1, rp = rl(rv, w3);
-      const int64_t o = (int64_t)((uint64_t)rl(off_lo, l) | (uint64_t)rl(off_hi, l) << 32);
-      const uint32_t t = (uint32_t)ldc(P.trips + o + (int64_t)rp - 1);
+      // the trip: entry rp - 1 of the loop's list; those of the parent's
+      // remaining iterations follow it, so up to 64 are read at once
+      if (!has_trip(l, rp - 1u)) {
+        retire_all();
+        read_trips(l, rp - 1u, rl(tv, w3) - rl(hv, w3));
+      }
+      const uint32_t t = rl(tw, rp - 1u - tw_first);
       tv = wl(tv, l, t);
       if (t == 0) {
         hv = wl(hv, l, 0u);
