@@ -32,7 +32,8 @@
 //     once and run without the dispatch, which is some 300 scalar instructions
 //     per iteration and trip on the general path and 40 here: thresholds, slots
 //     and tiles are carried incrementally, trips are read 64 at a time, and
-//     where the loop around it holds nothing else the trips follow one another.
+//     where the loop around it holds nothing else (or a no-op before it, an
+//     acquire) the trips follow one another.
 // The ring program (64 outer iterations, 4 slots, 1024 workgroups, 303 MB of
 // tiles) takes 164 us, 492 us with every instruction dispatched, and 1705 us
 // with tables, loop registers and execution counts read from memory and LDS and
@@ -329,16 +330,36 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
     bool ok = false, nest = false;
     uint32_t l = 0, a = 0, op = 0, slot1 = 0, wait = 0, n_waits = 0;
     InnerWait w0, w1;
+    bool pre = false;                      // a no-op before the loop in the loop around it (an acquire)
     int32_t a2 = 0, a4 = 0;
     uint32_t a3 = 0, a5 = 0, a6 = 0, src = 0, dst = 0;
     float k_const = 0.f;
   } F;
+  auto decode = [&](bool on, uint32_t row) __attribute__((always_inline)) {
+    InnerWait x;
+    if (on) {
+      const uint32_t q0 = wrow(row, 0);
+      x.addr = counter(q0 & 0xffu);
+      x.dep = wrow(row, 1);
+      x.k = wrow(row, 2);
+      x.lP = (q0 >> 8) & 0xffu;
+      x.lS = (q0 >> 16) & 0xffu;
+      x.mask = (q0 >> 24) & 1u;
+      x.N = (int32_t)wrow(row, 4);
+      x.c = x.N * (int32_t)wrow(row, 3) + (x.N - (int32_t)wrow(row, 5));
+    }
+    return x;
+  };
   // Runs the decoded loop from its first iteration of a trip on; returns the
   // code words it passes.
+  // (The no-op before the loop in the general form only: with a form of its own
+  // for wide loads the chain program took 214 us instead of 266, but the ring
+  // program, which has no such no-op, 181 instead of 168.)
   enum { LOAD_WIDE, SCALE_256, OTHER };
   auto run_inner = [&](auto which) __attribute__((always_inline)) -> uint32_t {
     constexpr int kWhich = decltype(which)::value;
-    const bool tiles = kWhich == LOAD_WIDE || (kWhich == OTHER && (F.op == 1u || F.op == 5u));
+    constexpr bool kWide = kWhich == LOAD_WIDE, kPre = kWhich == OTHER;
+    const bool tiles = kWide || (kWhich == OTHER && (F.op == 1u || F.op == 5u));
     const uint32_t l = F.l, a = F.a, own = counter(F.slot1 - 1u);
     uint32_t r = rl(rv, l), n = rl(tv, l);               // r of the trip's first iteration
     uint32_t ra = rl(rv, a), ha = rl(hv, a);
@@ -365,26 +386,46 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
       return x;
     };
     InnerWaitState x0 = start(F.w0, F.wait), x1 = start(F.w1, F.wait + 1u);
-    auto wait = [&](const InnerWait &w, InnerWaitState &x, uint32_t h) __attribute__((always_inline)) {
-      if (x.run > (int32_t)x.met && h > x.kk && !aborted) {
-        uint32_t polls = 0;
-        while (true) {
-          x.met = uniform(lds_poll(w.addr));
-          if ((int32_t)x.met >= x.run) break;
-          if (pending > 0) {
-            pending -= 1;
-            wait_at_most(pending * ops);
-            signal(1u);
-          } else if (++polls > limit) {
-            report_deadlock(P.err, w.dep, (uint32_t)wg, r - 1u, (uint32_t)x.run, x.met, (uint32_t)wave);
-            aborted = 1u;
-            break;
-          } else if (polls > 16u) {
-            __builtin_amdgcn_s_sleep(1);
-          }
+    auto block = [&](const InnerWait &w, InnerWaitState &x, uint32_t inst) __attribute__((always_inline)) {
+      uint32_t polls = 0;
+      while (true) {
+        x.met = uniform(lds_poll(w.addr));
+        if ((int32_t)x.met >= x.run) break;
+        if (pending > 0) {
+          pending -= 1;
+          wait_at_most(pending * ops);
+          signal(1u);
+        } else if (++polls > limit) {
+          report_deadlock(P.err, w.dep, (uint32_t)wg, inst, (uint32_t)x.run, x.met, (uint32_t)wave);
+          aborted = 1u;
+          break;
+        } else if (polls > 16u) {
+          __builtin_amdgcn_s_sleep(1);
         }
       }
+    };
+    auto wait = [&](const InnerWait &w, InnerWaitState &x, uint32_t h) __attribute__((always_inline)) {
+      if (x.run > (int32_t)x.met && h > x.kk && !aborted) block(w, x, r - 1u);
       x.run += x.step;
+    };
+    const bool pre = kPre && F.pre;
+    const uint32_t pre_slot1 = pre ? code(F.pc - 2u, 0) >> 24 : 0u, pre_wait = pre ? code(F.pc - 2u, 2) : 0u;
+    const uint32_t pre_n = pre ? code(F.pc - 2u, 3) : 0u;
+    const InnerWait p0 = decode(pre_n > 0u, pre_wait), p1 = decode(pre_n > 1u, pre_wait + 1u);
+    InnerWaitState y0 = start(p0, pre_wait), y1 = start(p1, pre_wait + 1u);
+    // a wait of the no-op, whose threshold is evaluated at each iteration
+    auto wait_pre = [&](const InnerWait &w, InnerWaitState &y) __attribute__((always_inline)) {
+      const uint32_t rP = w.lP == l ? r - 1u : w.lP == a ? ra + 0u : rl(rv, w.lP);
+      const uint32_t hS = w.lS == l ? n + 0u : w.lS == a ? ha + 0u : rl(hv, w.lS);
+      y.run = w.mask && hS <= w.k ? 0 : w.N * (int32_t)rP - w.c;
+      if (y.run > (int32_t)y.met && !aborted) block(w, y, ra - 1u);
+    };
+    auto flush = [&]() __attribute__((always_inline)) {
+      if (pending > 0) {
+        wait_vm<0>();
+        signal(pending);
+        pending = 0;
+      }
     };
     // slot and tile
     const bool p4 = F.a4 >= 0, p2 = F.a2 >= 0;
@@ -400,14 +441,14 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
         wait(F.w1, x1, h);
         const uint32_t slot = 4u * T * (s4 + s2 * mul2);
         if (tiles && !aborted) {
-          if (kWhich == LOAD_WIDE)
+          if (kWide)
             __builtin_amdgcn_global_load_lds((const void *)(P.x + tile + 4 * lane), (BFS_LDS void *)(uintptr_t)(F.dst + slot), 16, 0, 0);
           else if (F.op == 1u)
             load_tile(F.dst + slot, P.x + tile);
           else
             store_tile(F.src + slot, P.out + tile);
           if (pending >= most) {
-            if (kWhich == LOAD_WIDE) wait_vm<kMaxPending - 1>(); else wait_at_most(pending * ops);
+            if (kWide) wait_vm<kMaxPending - 1>(); else wait_at_most(pending * ops);
             signal(1u);
           } else {
             pending += 1;
@@ -424,15 +465,18 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
         tile += d6;
       }
       if (ha == ta) break;
-      // the next iteration of the loop around it, which holds nothing else
+      // the next iteration of the loop around it, which holds nothing else (but
+      // the no-op)
       ra += 1u;
       ha += 1u;
+      if (pre) {
+        wait_pre(p0, y0);
+        wait_pre(p1, y1);
+        flush();
+        add_slot(pre_slot1);
+      }
       if (!has_trip(l, ra - 1u)) {
-        if (pending > 0) {
-          wait_vm<0>();
-          signal(pending);
-          pending = 0;
-        }
+        flush();
         read_trips(l, ra - 1u, ta - ha);
       }
       n = rl(tw, ra - 1u - tw_first);
@@ -447,6 +491,8 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
     }
     if (F.n_waits > 0u && F.wait < 64u) seen = wl(seen, F.wait, x0.met);
     if (F.n_waits > 1u && F.wait + 1u < 64u) seen = wl(seen, F.wait + 1u, x1.met);
+    if (pre_n > 0u && pre_wait < 64u) seen = wl(seen, pre_wait, y0.met);
+    if (pre_n > 1u && pre_wait + 1u < 64u) seen = wl(seen, pre_wait + 1u, y1.met);
     queue = pending > 0 ? same & ((1ull << (8u * pending)) - 1ull) : 0ull;
     rv = wl(rv, l, r - 1u);
     hv = wl(hv, l, n);
@@ -473,31 +519,22 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
         F.wait = w2;
         F.n_waits = w3;
         F.l = code(pc + 1, 1);
-        // the loop around it, if it holds nothing but this loop
-        const uint32_t e0 = code(pc + 2, 0);
+        // the loop around it, if it holds nothing but this loop and at most a
+        // no-op before it
         F.a = pc > 0u ? code(pc - 1u, 3) : 0u;
-        F.nest = (e0 & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 2, 1) == F.a && code(pc + 2, 2) + 2u == pc &&
+        F.nest = (code(pc + 2, 0) & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 2, 1) == F.a &&
                  ((P.fallback_loops >> F.a) & 1u) == 0u;
+        const uint32_t first = code(pc + 2, 2) + 1u, n0 = pc > 1u ? code(pc - 2u, 0) : 0u;   // first word of its body
+        F.pre = F.nest && first + 2u == pc && (n0 & 0xffffu) == (uint32_t)bfs::CODE_INSTR && code(pc - 2u, 3) <= 2u;
+        F.nest = F.pre || (F.nest && first + 1u == pc);
         F.ok = (code(pc + 1, 0) & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 1, 2) + 1u == pc &&
                ((P.fallback_loops >> F.l) & 1u) == 0u && w3 <= 2u && (F.op == 1u || F.op == 2u || F.op == 4u || F.op == 5u);
-        auto decode = [&](uint32_t j) __attribute__((always_inline)) {
-          InnerWait x;
-          if (F.ok && j < w3) {
-            const uint32_t q0 = wrow(w2 + j, 0);
-            x.addr = counter(q0 & 0xffu);
-            x.dep = wrow(w2 + j, 1);
-            x.k = wrow(w2 + j, 2);
-            x.lP = (q0 >> 8) & 0xffu;
-            x.lS = (q0 >> 16) & 0xffu;
-            x.mask = (q0 >> 24) & 1u;
-            x.N = (int32_t)wrow(w2 + j, 4);
-            x.c = x.N * (int32_t)wrow(w2 + j, 3) + (x.N - (int32_t)wrow(w2 + j, 5));
-            F.ok = F.ok && wrow(w2 + j, 6) == 0u;            // (no snapshots)
-          }
-          return x;
-        };
-        F.w0 = decode(0u);
-        F.w1 = decode(1u);
+        // (waits on snapshots stay on the general path)
+        for (uint32_t w = w2; F.ok && w < w2 + w3; ++w) F.ok = wrow(w, 6) == 0u;
+        if (F.pre)
+          for (uint32_t w = code(pc - 2u, 2); F.ok && w < code(pc - 2u, 2) + code(pc - 2u, 3); ++w) F.ok = wrow(w, 6) == 0u;
+        F.w0 = decode(F.ok && w3 > 0u, w2);
+        F.w1 = decode(F.ok && w3 > 1u, w2 + 1u);
         if (F.ok) {
           F.a2 = (int32_t)arg(w1, 2);
           F.a3 = arg(w1, 3);
@@ -511,8 +548,8 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
         }
       }
       if (F.ok && rl(hv, F.l) == 1u) {
-        if (F.op == 1u && P.wide_x) pc += run_inner(std::integral_constant<int, LOAD_WIDE>{});
-        else if (F.op == 2u && T == 256u) pc += run_inner(std::integral_constant<int, SCALE_256>{});
+        if (F.op == 1u && P.wide_x && !F.pre) pc += run_inner(std::integral_constant<int, LOAD_WIDE>{});
+        else if (F.op == 2u && T == 256u && !F.pre) pc += run_inner(std::integral_constant<int, SCALE_256>{});
         else pc += run_inner(std::integral_constant<int, OTHER>{});
         continue;
       }

@@ -55,7 +55,8 @@ def _program(tile, slots, depth, acquire):
         b.dep("ACC", "LOAD", n, linear=linear)
         b.dep("STORE", "ADD", n, linear=linear)
     if acquire:
-        b.dep("ADD", "ACQ", 1)
+        if slots == "gen":                               # (three waits; STORE's implies it)
+            b.dep("ADD", "ACQ", 1)
         b.dep("ACC", "ACQ", 1)
         b.dep("STORE", "ACQ", 1)
     p = b.build()
