@@ -22,10 +22,11 @@
 //     stored, by blocks of 32 rows.  Blocks alternate between the MFMA waves
 //     that share a column block, so a unit with v valid blocks takes
 //     ceil(v / 2) blocks' MFMAs; units without valid rows are not run.
-//   * On small grids an item's units go to several workgroups.
+//   * An item's units go to several workgroups: on small grids to fill the
+//     compute units, on large ones to run together (they read the same weights).
 //
 // 32768 tokens, 64 experts, K = 4096 and 1408 (us of phase 1 and 2 with whole
-// items in single steps, then here): 1100 and 570, 1020 and 530.
+// items in single steps, then here): 1100 and 570, 963 and 515.
 #include <string>
 #include <type_traits>
 
@@ -53,6 +54,7 @@ struct Split {
   int32_t sm, sn;    // workgroups of an item: units of its rows in turn, column parts
   int32_t n_wg;      // items
   int32_t items;     // ... rounded up to a multiple of 8
+  int32_t sums;      // moe_many_kernel: byte offset of its sums in LDS
   int32_t slots;     // ring slots in LDS (even, at least the program's ring)
 };
 
@@ -443,6 +445,58 @@ __global__ void __launch_bounds__(768) moe_part_kernel(MoeParams P, Split D) {
   if (wg < D.n_wg) run_units<kPhase, kPM, 256>(P, D, lds, wg, blockIdx.x / D.items);
 }
 
+// More items: workgroups that stay, kPerXcd on each XCD.  The units of an XCD's
+// items (item w belongs to XCD w % 8), counted along the items in order, go to
+// its workgroups in turn, so that the units of an item, which read the same
+// weights, run at about the same time and share them in L2 (with a workgroup
+// per item each M-tile reads them from memory again), and the last round is
+// made of the smallest experts' units.  The sums of units up to each item are
+// kept in LDS behind the ring.
+constexpr int kPerXcd = 32, kFew = 512, kAlone = 1 << 20;   // kAlone: units of an item that far apart (one unit)
+
+template <int kPhase, int kPM>
+__global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int x = blockIdx.x % 8, n_x = D.items / 8;
+  const uint32_t sums = lds_addr(lds) + (uint32_t)D.sums;
+  uint32_t total = 0;
+  for (int c = 0; c < n_x; c += 64) {       // every wave counts, the first one writes
+    const int i = c + (int)lane_id(), item = 8 * i + x;
+    uint32_t upto = 0;
+    if (i < n_x && item < D.n_wg) {
+      const int32_t e = P.work[4 * item], mt0 = P.work[4 * item + 2];
+      const uint32_t trip_m = (uint32_t)P.trips[P.trip_off[(int64_t)item * 4 + 1]];
+      const int32_t left = P.eoff[e + 1] - P.eoff[e] - mt0 * D.bm;
+      const uint32_t rows = left <= 0 ? 0u : trip_m > (uint32_t)left / (uint32_t)D.bm ? (uint32_t)left : trip_m * (uint32_t)D.bm;
+      upto = (rows + kPM - 1u) / kPM;
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {      // inclusive sums
+      const uint32_t v = __shfl_up(upto, d);
+      if ((int)lane_id() >= d) upto += v;
+    }
+    upto += total;
+    if (threadIdx.x < 64 && i < n_x) *(BFS_LDS uint32_t *)(uintptr_t)(sums + 4u * (uint32_t)i) = upto;
+    total = __builtin_amdgcn_readlane(upto, 63);
+  }
+  int c = 0;
+  for (uint32_t unit = blockIdx.x / 8; unit < total; unit += kPerXcd) {
+    __syncthreads();                        // the sums are written; the unit before is done in every wave
+    uint64_t hit = 0;
+    uint32_t upto = 0;
+    while (true) {                          // the first item whose sum exceeds unit (unit < total: there is one)
+      const int i = min(c + (int)lane_id(), n_x - 1);
+      upto = *(const BFS_LDS uint32_t *)(uintptr_t)(sums + 4u * (uint32_t)i);
+      hit = __ballot(upto > unit);
+      if (hit != 0ull) break;
+      c += 64;
+    }
+    const int at = c + __builtin_ctzll(hit);
+    const uint32_t before = at > 0 ? uniform(*(const BFS_LDS uint32_t *)(uintptr_t)(sums + 4u * (uint32_t)(at - 1))) : 0u;
+    run_units<kPhase, kPM, 256>(P, D, lds, 8 * at + x, (int)(unit - before));
+  }
+}
+
 // At most kScan items: in quarters of 128 x 128 if these fit the compute units
 // at once, else as moe_part_kernel.  How many there are the routing decides, so
 // every wave counts them from the work list.  (us of phase 1 and 2 in whole
@@ -488,28 +542,30 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
   // step would then leave a pair's reuse one step short.
   const int slots = (P.ring + 1) & ~1, ksteps = P.kdim / kBK;
   if (linear && ksteps % 2 != 0) return false;
-  auto go = [&](auto part, auto small, auto unit) -> bool {
+  auto go = [&](auto part, auto many, auto small, auto unit) -> bool {
     using G = decltype(unit);
     const int chunks = phase == 1 ? G::kRB : 2 * G::kRB;
     const size_t ring = (size_t)slots * G::kSlot;
-    const size_t lds = kCntBytes + ring + (size_t)P.e_ring * kESlotBytes;
+    const size_t base = kCntBytes + ring + (size_t)P.e_ring * kESlotBytes;
+    // Up to four workgroups for an item's units (runs of four M-tiles) while
+    // the items are few; beyond kFew of them, workgroups that stay and take the
+    // units in turn: 32768 rows, 64 experts, K = 4096 and 1408, 1040 and 1520
+    // items: 1048 and 515 us with a workgroup per item, 963 and 515 us in turn
+    // (64 even experts: 967 and 465, 889 and 445); 8 experts, 352 and 512 items:
+    // 770 and 390 us split, 824 and 417 us in turn.
+    const bool is_small = n_wg <= kScan, is_many = n_wg > kFew;
+    const int items = (n_wg + 7) / 8 * 8, sm = is_many ? kAlone : 4;
+    const size_t lds = base + (is_many ? (size_t)items / 8 * 4 : 0);
     // (quarters take half of the ring and of the chunks or less)
     if (lds > 160 * 1024 || (P.e_ring == 0 && (size_t)chunks * kESlotBytes > ring)) return false;
-    // Runs of up to four M-tiles on as many workgroups where that makes up to
-    // 2048 of them: 8 experts, 32768 rows, K = 4096, 352 items 891 us, split
-    // 784 us; beyond, the launch is balanced without (64 experts, 1024 items
-    // of K = 1408: 478 and 519 us).
-    const bool is_small = n_wg <= kScan;
-    const int items = (n_wg + 7) / 8 * 8, sm = n_wg <= 512 ? 4 : 1;
-    const int subs = is_small ? kQuarterM * kQuarterN : sm;
-    const void *kern = is_small ? (const void *)small : (const void *)part;
-    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const int grid = is_many ? 8 * kPerXcd : items * (is_small ? kQuarterM * kQuarterN : sm);
+    const auto kern = is_many ? many : is_small ? small : part;
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) {
       st = bfs::fail(BFS_E_DEVICE, std::string("moe attribute: ") + hipGetErrorString(e));
       return true;
     }
-    hipLaunchKernelGGL(is_small ? small : part, dim3(items * subs), dim3(64 * kWaves), lds, s, P,
-                       Split{bm, sm, 1, n_wg, items, slots});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), lds, s, P, Split{bm, sm, 1, n_wg, items, (int)base, slots});
     e = hipGetLastError();
     st = e == hipSuccess ? BFS_OK : bfs::fail(BFS_E_DEVICE, std::string("moe launch: ") + hipGetErrorString(e));
     return true;
@@ -519,8 +575,8 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
   // 1408: 206 and 155, 151 and 82, 183 and 85.  M-tiles of 128 rows, 32
   // experts, K = 2048 and 1024: 187 and 98, units of 128: 171 and 93.)
   if (bm == 128)
-    return phase == 1 ? go(moe_part_kernel<1, 128>, moe_small_kernel<1, 128>, Unit<128, 256>{})
-                      : go(moe_part_kernel<2, 128>, moe_small_kernel<2, 128>, Unit<128, 256>{});
-  return phase == 1 ? go(moe_part_kernel<1, 256>, moe_small_kernel<1, 256>, Unit<256, 256>{})
-                    : go(moe_part_kernel<2, 256>, moe_small_kernel<2, 256>, Unit<256, 256>{});
+    return phase == 1 ? go(moe_part_kernel<1, 128>, moe_many_kernel<1, 128>, moe_small_kernel<1, 128>, Unit<128, 256>{})
+                      : go(moe_part_kernel<2, 128>, moe_many_kernel<2, 128>, moe_small_kernel<2, 128>, Unit<128, 256>{});
+  return phase == 1 ? go(moe_part_kernel<1, 256>, moe_many_kernel<1, 256>, moe_small_kernel<1, 256>, Unit<256, 256>{})
+                    : go(moe_part_kernel<2, 256>, moe_many_kernel<2, 256>, moe_small_kernel<2, 256>, Unit<256, 256>{});
 }
