@@ -38,14 +38,19 @@ PROFILES = os.path.join(ROOT, "profiles")
 # its barrier-free, uninstrumented dispatch in rocprofv3 output
 KERNELS = {
     "stream3": (["kern_stream3.hip", "device_sync.h", "bfs_internal.h"], ["stream3_kernel<0, false"]),
-    "gemm": (["kern_gemm.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["gemm_kernel<0, false, 1, 0>"]),
+    "gemm": (["kern_gemm.hip", "kern_gemm_part.hip", "gemm_common.h", "engine_sync.h", "device_sync.h", "bfs_internal.h"],
+             ["gemm_part_kernel<256, 256>"]),
     "attn": (["kern_attn.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["attn_kernel<0, false>"]),
     "rms": (["kern_rms.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["rms_kernel<0, false, 4>"]),
     "adamw": (["kern_adamw.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["adamw_kernel<0, false>"]),
-    "moe": (["kern_moe.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"],
-            ["moe_kernel<1, 0, false, 256>", "moe_kernel<2, 0, false, 256>"]),
+    "moe": (["kern_moe.hip", "kern_moe_part.hip", "moe_common.h", "engine_sync.h", "device_sync.h", "bfs_internal.h"],
+            ["moe_many_kernel<1, 256>", "moe_many_kernel<2, 256>"]),
     "chain": (["kern_chain.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["chain_kernel<0, false>"]),
 }
+# how the kernels of each family are called in rocprofv3 output
+STEMS = {"stream3": ["stream3_kernel<"], "gemm": ["gemm_kernel<", "gemm_part_kernel<", "gemm_mixed_kernel<"],
+         "attn": ["attn_kernel<"], "moe": ["moe_kernel<", "moe_many_kernel<", "moe_part_kernel<", "moe_small_kernel<"],
+         "rms": ["rms_kernel<"], "adamw": ["adamw_kernel<"], "chain": ["chain_kernel<"]}
 COPY_NAMES = ("__amd_rocclr_copyBuffer",)   # the runtime's device-to-device copy
 
 
@@ -148,11 +153,11 @@ def trace(args):
     for c in args.command:
         lines += ["```", c, "```", ""]
     lines += ["Template arguments: <mode, instrumented> (mode 0 = barrier-free, 1 = barrier); "
-              "MoE: <phase, mode, instrumented>.  `interp_kernel` is the generic interpreter "
-              "(mode and instrumentation are run-time arguments there).", "",
+              "MoE: <phase, mode, instrumented>.  `gemm_part` / `gemm_mixed` <rows, columns of a part> and "
+              "`moe_many` / `moe_part` / `moe_small` <phase, rows of a unit> are barrier-free; "
+              "`interp_kernel` <mode, instrumented, program in registers> is the generic interpreter.", "",
               "| Kernel | Calls | Average ns | Min ns | Max ns |", "|---|---|---|---|---|"]
-    stems = ("stream3_kernel<", "gemm_kernel<", "attn_kernel<", "moe_kernel<", "rms_kernel<", "adamw_kernel<",
-             "chain_kernel<", "interp_kernel")
+    stems = [t for ts in STEMS.values() for t in ts] + ["interp_kernel"]
     for r in rows:
         name = r["Name"]
         if not any(t in name for t in stems):
@@ -195,17 +200,15 @@ def sq(args):
     uninstrumented kernel instantiation of the family, with the shader clock
     (GRBM_GUI_ACTIVE per XCD over the dispatch's duration) and the MFMA and
     LDS busy shares of the clock cycles when those counters are present."""
-    stem = {"stream3": "stream3_kernel<", "gemm": "gemm_kernel<", "attn": "attn_kernel<",
-            "moe": "moe_kernel<", "rms": "rms_kernel<", "adamw": "adamw_kernel<",
-            "chain": "chain_kernel<"}[args.kernel]
+    stems = STEMS[args.kernel]
     table = {}          # kernel -> counter -> (mean, dispatches)
     clock = {}          # kernel -> (GRBM_GUI_ACTIVE per XCD, mean dispatch duration)
     for d in args.dir:
         rows = _counter_rows(d)
-        names = sorted({r["Kernel_Name"] for r in rows if stem in r["Kernel_Name"]})
+        names = sorted({r["Kernel_Name"] for r in rows if any(t in r["Kernel_Name"] for t in stems)})
         counters = sorted({r["Counter_Name"] for r in rows})
         for n in names:
-            short = n[n.index(stem):].split("(")[0]
+            short = next(n[n.index(t):].split("(")[0] for t in stems if t in n)
             if ", true" in short:
                 continue
             for c in counters:
