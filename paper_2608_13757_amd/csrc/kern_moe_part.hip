@@ -26,7 +26,7 @@
 //     compute units, on large ones to run together (they read the same weights).
 //
 // 32768 tokens, 64 experts, K = 4096 and 1408 (us of phase 1 and 2 with whole
-// items in single steps, then here): 1100 and 570, 963 and 515.
+// items in single steps, then here): 1100 and 570, 951 and 497.
 #include <string>
 #include <type_traits>
 
@@ -54,7 +54,7 @@ struct Split {
   int32_t sm, sn;    // workgroups of an item: units of its rows in turn, column parts
   int32_t n_wg;      // items
   int32_t items;     // ... rounded up to a multiple of 8
-  int32_t sums;      // moe_many_kernel: byte offset of its sums in LDS
+  int32_t table;     // moe_many_kernel: byte offset of its items in LDS
   int32_t slots;     // ring slots in LDS (even, at least the program's ring)
 };
 
@@ -62,9 +62,28 @@ struct Split {
 // one chunk cover all banks.
 __device__ __forceinline__ uint32_t swz128(uint32_t row, uint32_t c) { return row * 128u + ((c ^ ((row >> 1) & 7u)) << 4); }
 
+// A work item: its expert, first output column and M-tile, the expert's first
+// grouped row and row count, and the M loop's trip.
+struct Item {
+  int32_t expert, n0, mt0, e_lo, e_cnt;
+  uint32_t trip_m;
+};
+
+__device__ __forceinline__ Item read_item(const MoeParams &P, int wg) {
+  Item x;
+  x.expert = ldc(P.work + 4 * wg + 0);
+  x.n0 = ldc(P.work + 4 * wg + 1);
+  x.mt0 = ldc(P.work + 4 * wg + 2);
+  x.e_lo = ldc(P.eoff + x.expert);
+  x.e_cnt = ldc(P.eoff + x.expert + 1) - x.e_lo;
+  x.trip_m = (uint32_t)ldc(P.trips + ldc(P.trip_off + (int64_t)wg * 4 + 1));
+  return x;
+}
+
 // The units of item wg that fall to its workgroup sub (of sm * sn).
 template <int kPhase, int kPM, int kPN>
-__device__ __forceinline__ void run_units(const MoeParams &P, const Split &D, unsigned char *lds, int wg, int sub) {
+__device__ __forceinline__ void run_units(const MoeParams &P, const Split &D, unsigned char *lds, int wg, int sub,
+                                          const Item &I) {
   using G = Unit<kPM, kPN>;
   uint32_t *cnt = reinterpret_cast<uint32_t *>(lds);
   const uint32_t ring = lds_addr(lds) + kCntBytes;
@@ -73,12 +92,10 @@ __device__ __forceinline__ void run_units(const MoeParams &P, const Split &D, un
   const int sm = sub / D.sn, sn = sub % D.sn;
   const int wave = wave_id();
   const uint32_t lane = lane_id(), l32 = lane & 31u, lhi = lane >> 5;
-  const int32_t expert = ldc(P.work + 4 * wg + 0);
-  const int32_t n0 = ldc(P.work + 4 * wg + 1) + sn * (kPhase == 1 ? kPN / 2 : kPN);
-  const int32_t mt0 = ldc(P.work + 4 * wg + 2);
-  const int32_t e_lo = ldc(P.eoff + expert), e_cnt = ldc(P.eoff + expert + 1) - e_lo;
+  const int32_t expert = I.expert, mt0 = I.mt0, e_lo = I.e_lo, e_cnt = I.e_cnt;
+  const int32_t n0 = I.n0 + sn * (kPhase == 1 ? kPN / 2 : kPN);
   const int64_t *toff = P.trip_off + (int64_t)wg * 4;
-  uint32_t trip_m = (uint32_t)ldc(P.trips + ldc(toff + 1));
+  uint32_t trip_m = I.trip_m;
   const int64_t k_off = ldc(toff + 2), c_off = ldc(toff + 3);
   const uint32_t ksteps = (uint32_t)(P.kdim / kBK);
   const uint32_t max_m = (uint32_t)max(0, (e_cnt + D.bm - 1) / D.bm - mt0);
@@ -442,58 +459,68 @@ template <int kPhase, int kPM>
 __global__ void __launch_bounds__(768) moe_part_kernel(MoeParams P, Split D) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int wg = blockIdx.x % D.items;
-  if (wg < D.n_wg) run_units<kPhase, kPM, 256>(P, D, lds, wg, blockIdx.x / D.items);
+  if (wg < D.n_wg) run_units<kPhase, kPM, 256>(P, D, lds, wg, blockIdx.x / D.items, read_item(P, wg));
 }
 
-// More items: workgroups that stay, kPerXcd on each XCD.  The units of an XCD's
+// Many items: workgroups that stay, kPerXcd on each XCD.  The units of an XCD's
 // items (item w belongs to XCD w % 8), counted along the items in order, go to
 // its workgroups in turn, so that the units of an item, which read the same
 // weights, run at about the same time and share them in L2 (with a workgroup
 // per item each M-tile reads them from memory again), and the last round is
-// made of the smallest experts' units.  The sums of units up to each item are
-// kept in LDS behind the ring.
-constexpr int kPerXcd = 32, kFew = 512, kAlone = 1 << 20;   // kAlone: units of an item that far apart (one unit)
+// made of the smallest experts' units.  The items and the sums of units up to
+// each are kept in LDS behind the ring (read from memory for each unit they
+// cost it some microseconds).
+constexpr int kPerXcd = 32, kAlone = 1 << 20;   // kAlone: units of an item that far apart (one unit)
 
 template <int kPhase, int kPM>
 __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int x = blockIdx.x % 8, n_x = D.items / 8;
-  const uint32_t sums = lds_addr(lds) + (uint32_t)D.sums;
+  const uint32_t table = lds_addr(lds) + (uint32_t)D.table;
   uint32_t total = 0;
   for (int c = 0; c < n_x; c += 64) {       // every wave counts, the first one writes
     const int i = c + (int)lane_id(), item = 8 * i + x;
     uint32_t upto = 0;
+    u32x4 w{}, v{};
     if (i < n_x && item < D.n_wg) {
-      const int32_t e = P.work[4 * item], mt0 = P.work[4 * item + 2];
+      const int32_t e = P.work[4 * item], n0 = P.work[4 * item + 1], mt0 = P.work[4 * item + 2];
       const uint32_t trip_m = (uint32_t)P.trips[P.trip_off[(int64_t)item * 4 + 1]];
-      const int32_t left = P.eoff[e + 1] - P.eoff[e] - mt0 * D.bm;
+      const int32_t e_lo = P.eoff[e], e_cnt = P.eoff[e + 1] - e_lo, left = e_cnt - mt0 * D.bm;
       const uint32_t rows = left <= 0 ? 0u : trip_m > (uint32_t)left / (uint32_t)D.bm ? (uint32_t)left : trip_m * (uint32_t)D.bm;
       upto = (rows + kPM - 1u) / kPM;
+      w = u32x4{(uint32_t)e, (uint32_t)n0, (uint32_t)mt0, (uint32_t)e_lo};
+      v = u32x4{(uint32_t)e_cnt, trip_m, 0u, 0u};
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {      // inclusive sums
-      const uint32_t v = __shfl_up(upto, d);
-      if ((int)lane_id() >= d) upto += v;
+      const uint32_t u = __shfl_up(upto, d);
+      if ((int)lane_id() >= d) upto += u;
     }
     upto += total;
-    if (threadIdx.x < 64 && i < n_x) *(BFS_LDS uint32_t *)(uintptr_t)(sums + 4u * (uint32_t)i) = upto;
+    v.z = upto;
+    if (threadIdx.x < 64 && i < n_x) {
+      *(BFS_LDS u32x4 *)(uintptr_t)(table + 32u * (uint32_t)i) = w;
+      *(BFS_LDS u32x4 *)(uintptr_t)(table + 32u * (uint32_t)i + 16u) = v;
+    }
     total = __builtin_amdgcn_readlane(upto, 63);
   }
   int c = 0;
   for (uint32_t unit = blockIdx.x / 8; unit < total; unit += kPerXcd) {
-    __syncthreads();                        // the sums are written; the unit before is done in every wave
+    __syncthreads();                        // the table is written; the unit before is done in every wave
     uint64_t hit = 0;
-    uint32_t upto = 0;
     while (true) {                          // the first item whose sum exceeds unit (unit < total: there is one)
       const int i = min(c + (int)lane_id(), n_x - 1);
-      upto = *(const BFS_LDS uint32_t *)(uintptr_t)(sums + 4u * (uint32_t)i);
-      hit = __ballot(upto > unit);
+      hit = __ballot(*(const BFS_LDS uint32_t *)(uintptr_t)(table + 32u * (uint32_t)i + 24u) > unit);
       if (hit != 0ull) break;
       c += 64;
     }
     const int at = c + __builtin_ctzll(hit);
-    const uint32_t before = at > 0 ? uniform(*(const BFS_LDS uint32_t *)(uintptr_t)(sums + 4u * (uint32_t)(at - 1))) : 0u;
-    run_units<kPhase, kPM, 256>(P, D, lds, 8 * at + x, (int)(unit - before));
+    const u32x4 w = *(const BFS_LDS u32x4 *)(uintptr_t)(table + 32u * (uint32_t)at);
+    const u32x4 v = *(const BFS_LDS u32x4 *)(uintptr_t)(table + 32u * (uint32_t)at + 16u);
+    const uint32_t before = at > 0 ? uniform(*(const BFS_LDS uint32_t *)(uintptr_t)(table + 32u * (uint32_t)at - 8u)) : 0u;
+    const Item I{(int32_t)uniform(w.x), (int32_t)uniform(w.y), (int32_t)uniform(w.z), (int32_t)uniform(w.w),
+                 (int32_t)uniform(v.x), uniform(v.y)};
+    run_units<kPhase, kPM, 256>(P, D, lds, 8 * at + x, (int)(unit - before), I);
   }
 }
 
@@ -527,9 +554,9 @@ __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
     Split Q = D;
     Q.sm = kQuarterM;
     Q.sn = kQuarterN;
-    run_units<kPhase, 128, 128>(P, Q, lds, wg, sub);
+    run_units<kPhase, 128, 128>(P, Q, lds, wg, sub, read_item(P, wg));
   } else if (sub < D.sm) {
-    run_units<kPhase, kPM, 256>(P, D, lds, wg, sub);
+    run_units<kPhase, kPM, 256>(P, D, lds, wg, sub, read_item(P, wg));
   }
 }
 
@@ -548,14 +575,20 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
     const size_t ring = (size_t)slots * G::kSlot;
     const size_t base = kCntBytes + ring + (size_t)P.e_ring * kESlotBytes;
     // Up to four workgroups for an item's units (runs of four M-tiles) while
-    // the items are few; beyond kFew of them, workgroups that stay and take the
-    // units in turn: 32768 rows, 64 experts, K = 4096 and 1408, 1040 and 1520
-    // items: 1048 and 515 us with a workgroup per item, 963 and 515 us in turn
-    // (64 even experts: 967 and 465, 889 and 445); 8 experts, 352 and 512 items:
-    // 770 and 390 us split, 824 and 417 us in turn.
-    const bool is_small = n_wg <= kScan, is_many = n_wg > kFew;
-    const int items = (n_wg + 7) / 8 * 8, sm = is_many ? kAlone : 4;
-    const size_t lds = base + (is_many ? (size_t)items / 8 * 4 : 0);
+    // the items are few; beyond `few` of them, workgroups that stay and take the
+    // units in turn.  Phase 1 gains from its first grid of more than a round of
+    // units (us split and in turn, items in brackets): [224] 145 and 109, [248]
+    // 413 and 363, [304] 483 and 448, [352] 770 and 824, [376] 117 and 129,
+    // [448] 88 and 67, [1040] 1048 and 951 (a workgroup per item).  Phase 2's
+    // units are shorter and store twice the chunks: [176] 44 and 48, [312] 214
+    // and 220, [448] 254 and 233, [512] 390 and 417, [720] 349 and 254, [1520]
+    // 515 and 497.
+    const int few = phase == 1 ? kScan : 512;
+    const int items = (n_wg + 7) / 8 * 8;
+    const size_t table = (size_t)items / 8 * 32;
+    const bool is_small = n_wg <= kScan, is_many = n_wg > few && base + table <= 160 * 1024;
+    const int sm = is_many ? kAlone : n_wg > 512 ? 1 : 4;
+    const size_t lds = base + (is_many ? table : 0);
     // (quarters take half of the ring and of the chunks or less)
     if (lds > 160 * 1024 || (P.e_ring == 0 && (size_t)chunks * kESlotBytes > ring)) return false;
     const int grid = is_many ? 8 * kPerXcd : items * (is_small ? kQuarterM * kQuarterN : sm);

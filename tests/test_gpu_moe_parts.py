@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 RAGGED = [300, 0, 129, 1, 530, 33, 256, 31]
 # (counts, K, N, bm, mchunk, options); N is a multiple of both phases' tiles.
 # Quarters where 2 sum ceil(rows / 128) N-tiles <= 256, units on several
-# workgroups of their item up to 512 items, in turn beyond; K steps: one, odd,
-# even.
+# workgroups of their item up to 128 items (phase 2: 512), in turn beyond; K
+# steps: one, odd, even.
 CASES = {
     "quarters": (RAGGED, 256, 256, 256, None, {}),
     "quarters_one_step": (RAGGED, 32, 256, 256, None, {}),
@@ -35,6 +35,7 @@ CASES = {
     "items": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 160, 16384, 256, 1, {}),
     "items_128_linear": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 192, 16384, 128, 2, {"linear": True, "e_ring": 1}),
     "items_long_runs": ([1100, 900, 255, 257, 64, 1, 0, 700], 96, 20480, 256, 9, {}),
+    "items_phases": ([1100, 900, 255, 257, 64, 1, 0, 700], 224, 6144, 256, None, {}),
     "linear_odd_k": (RAGGED, 96, 256, 256, None, {"linear": True}),      # stays whole
 }
 
