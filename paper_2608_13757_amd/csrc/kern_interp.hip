@@ -127,7 +127,7 @@ __device__ __forceinline__ void wait_at_most(uint32_t n) {
 // kLanes: the engine's code words, instruction rows and wait rows each fit
 // the 64 lanes of a register (the launcher checks); otherwise they are read
 // with scalar loads.
-template <int kMode, bool kInstr, bool kLanes>
+template <int kMode, bool kInstr, bool kLanes, bool kInner = false>
 __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   uint32_t *cnt = reinterpret_cast<uint32_t *>(lds);            // [64 slots][8 waves]
@@ -511,7 +511,8 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
     // loop of an engine): all that the general path below decodes for each
     // instruction and loop end is decoded once for the loop and evaluated once
     // per trip, and the iterations of a trip follow one another.
-    if (kMode == BFS_MODE_BARRIER_FREE && !kInstr && kind == bfs::CODE_INSTR && !aborted) {
+    if (kInner && kind == bfs::CODE_INSTR && !aborted &&
+        (code(pc + 1, 0) & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 1, 2) + 1u == pc) {
       if (pc != F.pc) {
         F.pc = pc;
         F.op = (w0 >> 8) & 0xffu;
@@ -527,8 +528,8 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
         const uint32_t first = code(pc + 2, 2) + 1u, n0 = pc > 1u ? code(pc - 2u, 0) : 0u;   // first word of its body
         F.pre = F.nest && first + 2u == pc && (n0 & 0xffffu) == (uint32_t)bfs::CODE_INSTR && code(pc - 2u, 3) <= 2u;
         F.nest = F.pre || (F.nest && first + 1u == pc);
-        F.ok = (code(pc + 1, 0) & 0xffu) == (uint32_t)bfs::CODE_END && code(pc + 1, 2) + 1u == pc &&
-               ((P.fallback_loops >> F.l) & 1u) == 0u && w3 <= 2u && (F.op == 1u || F.op == 2u || F.op == 4u || F.op == 5u);
+        F.ok = ((P.fallback_loops >> F.l) & 1u) == 0u && w3 <= 2u &&
+               (F.op == 1u || F.op == 2u || F.op == 4u || F.op == 5u);
         // (waits on snapshots stay on the general path)
         for (uint32_t w = w2; F.ok && w < w2 + w3; ++w) F.ok = wrow(w, 6) == 0u;
         if (F.pre)
@@ -787,6 +788,26 @@ bfs_status launch_interp(const bfs_plan *p, DevImage *img, const void *const *bu
   }
   if (instr)
     return lanes ? go(interp_kernel<BFS_MODE_BARRIER_FREE, true, true>) : go(interp_kernel<BFS_MODE_BARRIER_FREE, true, false>);
+  // The kernel with inner loops run without dispatch, if a loop of the program
+  // is one and no engine tracks another's instances: those engines' loops hold
+  // further words and stay on the general path, and the slowest engine sets the
+  // pace (us with these loops and without: ring program, a counter per engine,
+  // 256 workgroups 856 and 696, chain program, 191 workgroups 52.4 and 43.6;
+  // a counter per loop, ring, 1024 workgroups 167 and 513, chain 269 and 655).
+  bool inner = false, tracks = false;
+  for (int e = 0; e < p->n_engines; ++e)
+    for (int32_t pc = 0, n = p->code_off[e + 1] - p->code_off[e]; pc < n; ++pc) {
+      const int32_t *w = &p->code[4 * (size_t)(p->code_off[e] + pc)];
+      tracks = tracks || w[0] == CODE_TRACK || w[0] == CODE_SNAP;
+      if (w[0] != CODE_INSTR || pc + 1 == n || w[4] != CODE_END || w[6] + 1 != pc) continue;
+      const int32_t op = p->instr_opcode[w[1]];
+      inner = inner || (((p->fallback_loops >> w[5]) & 1u) == 0u && (op == 1 || op == 2 || op == 4 || op == 5) &&
+                        p->instr_wait_off[w[1] + 1] - p->instr_wait_off[w[1]] <= 2);
+    }
+  inner = inner && !tracks;
+  if (inner)
+    return lanes ? go(interp_kernel<BFS_MODE_BARRIER_FREE, false, true, true>)
+                 : go(interp_kernel<BFS_MODE_BARRIER_FREE, false, false, true>);
   return lanes ? go(interp_kernel<BFS_MODE_BARRIER_FREE, false, true>) : go(interp_kernel<BFS_MODE_BARRIER_FREE, false, false>);
 }
 
