@@ -55,7 +55,7 @@ struct Split {
   int32_t n_wg;      // items
   int32_t items;     // ... rounded up to a multiple of 8
   int32_t table;     // moe_many_kernel: byte offset of its items in LDS
-  int32_t slots;     // ring slots in LDS (even, at least the program's ring)
+  int32_t slots;     // ring slots in LDS (even)
 };
 
 // Byte offset of 16-byte chunk c (0 .. 7) of a 128-byte row: 16 rows read at
@@ -188,7 +188,7 @@ __device__ __forceinline__ void run_units(const MoeParams &P, const Split &D, un
         const uint32_t n = min(ksteps - it, 2u);
         g.r2 = k0 + it + n;
         g.h2 = it + n;
-        S.wait_affine(sb, P.load, g, it + n, g.r2 - 1, [] {});
+        S.wait_affine(sb, P.load, g, it + 2u, g.r2 - 1, [] {});   // (a single last step's pair of slots too)
         if (!S.aborted) {
           uint32_t sl = pslot + (it >> 1);
           sl -= sl >= pairs ? (sl / pairs) * pairs : 0u;
@@ -526,48 +526,94 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
 
 // At most kScan items: in quarters of 128 x 128 if these fit the compute units
 // at once, else as moe_part_kernel.  How many there are the routing decides, so
-// every wave counts them from the work list.  (us of phase 1 and 2 in whole
-// units, in quarters: 8 experts of 128 rows, K = 2048 and 1408, 176 and 128
-// quarters, 43 and 33, 33 and 25; 2048 ragged rows, K = 1024 and 1408, 440 and
-// 160 quarters, 31 and 39, 38 and 25.)
+// every wave counts them from the items' trips, and finds the workgroup's own
+// in the sums: a workgroup per possible quarter of every item (16) would cost
+// 1 us per 256 of them that have none (32 experts, 280 rows, K = 768 and 512:
+// both phases 50 us, so 35).  (us of phase 1 and 2 in whole units, in quarters:
+// 8 experts of 128 rows, K = 2048 and 1408, 176 and 128 quarters, 43 and 33, 33
+// and 25; 2048 ragged rows, K = 1024 and 1408, 440 and 160 quarters, 31 and 39,
+// 38 and 25.)
 constexpr int kScan = 128, kCUs = 256;
-constexpr int kQuarterM = 8, kQuarterN = 2;       // workgroups of an item in quarters (as many as it can have)
 
 template <int kPhase, int kPM>
 __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int wg = blockIdx.x % D.items, sub = blockIdx.x / D.items;
-  if (wg >= D.n_wg) return;
-  uint32_t quarters = 0;
+  // (both halves' loads first: two levels deep, from cold lines)
+  int32_t mt0[kScan / 64], lo[kScan / 64], hi[kScan / 64];
+  uint32_t trip[kScan / 64];
+  {
+    int32_t e[kScan / 64];
+    int64_t at[kScan / 64];
 #pragma unroll
-  for (int h = 0; h < kScan / 64; ++h) {
-    const int i = 64 * h + (int)lane_id();
-    if (i < D.n_wg) {
-      const int32_t e = P.work[4 * i], mt0 = P.work[4 * i + 2], n_mt = P.work[4 * i + 3];
-      const int32_t rows = min(P.eoff[e + 1] - P.eoff[e] - mt0 * D.bm, n_mt * D.bm);
-      if (rows > 0) quarters += 2u * (((uint32_t)rows + 127u) / 128u);
+    for (int h = 0; h < kScan / 64; ++h) {
+      const int i = min(64 * h + (int)lane_id(), D.n_wg - 1);
+      e[h] = P.work[4 * i];
+      mt0[h] = P.work[4 * i + 2];
+      at[h] = P.trip_off[(int64_t)i * 4 + 1];
+    }
+#pragma unroll
+    for (int h = 0; h < kScan / 64; ++h) {
+      lo[h] = P.eoff[e[h]];
+      hi[h] = P.eoff[e[h] + 1];
+      trip[h] = (uint32_t)P.trips[at[h]];
     }
   }
+  // quarters up to and with items lane and 64 + lane (an item without rows but
+  // with a trip has two, so that the trip is checked as any other's)
+  uint32_t own[kScan / 64], upto[kScan / 64], quarters = 0;
 #pragma unroll
-  for (int x = 32; x >= 1; x >>= 1) quarters += __shfl_xor(quarters, x);
-  if (uniform(quarters) <= (uint32_t)kCUs) {
-    Split Q = D;
-    Q.sm = kQuarterM;
-    Q.sn = kQuarterN;
-    run_units<kPhase, 128, 128>(P, Q, lds, wg, sub, read_item(P, wg));
-  } else if (sub < D.sm) {
-    run_units<kPhase, kPM, 256>(P, D, lds, wg, sub, read_item(P, wg));
+  for (int h = 0; h < kScan / 64; ++h) {
+    // (32 bits: rows first cut to the expert's, trips to as many tiles)
+    const int32_t left = max(hi[h] - lo[h] - mt0[h] * D.bm, 0);
+    const uint32_t rows = trip[h] > (uint32_t)left ? (uint32_t)left : min((uint32_t)left, trip[h] * (uint32_t)D.bm);
+    own[h] = 64 * h + (int)lane_id() < D.n_wg && trip[h] != 0u ? 2u * max((rows + 127u) / 128u, 1u) : 0u;
+    upto[h] = own[h];
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const uint32_t below = __shfl_up(upto[h], x);
+      upto[h] += (int)lane_id() >= x ? below : 0u;
+    }
+    upto[h] += quarters;
+    quarters = uniform(__shfl(upto[h], 63));
   }
+  if (quarters <= (uint32_t)kCUs) {
+    // quarter q here: neighbours in q (an item's) on one XCD
+    const uint32_t per = (quarters + 7u) / 8u, q = (blockIdx.x % 8u) * per + blockIdx.x / 8u;
+    if (blockIdx.x / 8u >= per || q >= quarters) return;
+    int wg = 0;
+    uint32_t sub = 0, parts = 2;
+#pragma unroll
+    for (int h = kScan / 64 - 1; h >= 0; --h) {
+      const uint64_t above = __ballot(upto[h] > q);
+      if (above != 0ull) {
+        const int at = __builtin_ctzll(above);
+        wg = 64 * h + at;
+        parts = uniform(__shfl(own[h], at));
+        sub = q - (uniform(__shfl(upto[h], at)) - parts);
+      }
+    }
+    Split Q = D;
+    Q.sm = (int32_t)(parts / 2u);
+    Q.sn = 2;
+    run_units<kPhase, 128, 128>(P, Q, lds, wg, (int)sub, read_item(P, wg));
+    return;
+  }
+  const int wg = blockIdx.x % D.items, sub = blockIdx.x / D.items;
+  if (wg < D.n_wg && sub < D.sm) run_units<kPhase, kPM, 256>(P, D, lds, wg, sub, read_item(P, wg));
 }
 
 }  // namespace
 
 bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, int n_wg, hipStream_t s, bfs_status &st) {
-  // Pairs of steps need an even number of ring slots, at least the program's
-  // ring (more slots than the program's distance orders only wait longer).
-  // Read linearized, MMA->LOAD counts steps across M-tiles: a single last
-  // step would then leave a pair's reuse one step short.
-  const int slots = (P.ring + 1) & ~1, ksteps = P.kdim / kBK;
+  // Pairs of steps take an even number of ring slots, one less than an odd
+  // ring (one more does not fit beside the epilogue slots of M-tiles of 128:
+  // whole items instead, 16384 tokens, 32 experts, K = 4096 and 1408: 1167 us
+  // of both phases, in four slots 885).  A pair at steps s and s + 1 waits for
+  // the MMAs of step s + 1 - ring, and MMA retires steps in twos from the start
+  // of a unit: with an odd ring that step is the first of its two, so the pair
+  // ring - 1 before is free.  Read linearized, MMA->LOAD counts steps across
+  // M-tiles, where a single last step would break the twos.
+  const int slots = P.ring & ~1, ksteps = P.kdim / kBK;
   if (linear && ksteps % 2 != 0) return false;
   auto go = [&](auto part, auto many, auto small, auto unit) -> bool {
     using G = decltype(unit);
@@ -591,7 +637,7 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
     const size_t lds = base + (is_many ? table : 0);
     // (quarters take half of the ring and of the chunks or less)
     if (lds > 160 * 1024 || (P.e_ring == 0 && (size_t)chunks * kESlotBytes > ring)) return false;
-    const int grid = is_many ? 8 * kPerXcd : items * (is_small ? kQuarterM * kQuarterN : sm);
+    const int grid = is_many ? 8 * kPerXcd : is_small && items * sm < kCUs ? kCUs : items * sm;
     const auto kern = is_many ? many : is_small ? small : part;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) {

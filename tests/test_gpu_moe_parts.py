@@ -36,6 +36,12 @@ CASES = {
     "items_128_linear": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 192, 16384, 128, 2, {"linear": True, "e_ring": 1}),
     "items_long_runs": ([1100, 900, 255, 257, 64, 1, 0, 700], 96, 20480, 256, 9, {}),
     "items_phases": ([1100, 900, 255, 257, 64, 1, 0, 700], 224, 6144, 256, None, {}),
+    "quarters_128_odd_k": (RAGGED, 352, 256, 128, None, {}),
+    "quarters_padded": ([40, 0, 0, 129, 0, 7, 300, 1], 160, 512, 128, 1, {"ring": 3, "e_ring": 1}),
+    "quarters_all_cus": ([128, 127, 1, 65] * 8, 96, 1024, 128, None, {"linear": False}),
+    "split_128_linear_odd_ring": ([1100, 900, 255, 257, 64, 1, 0, 700], 192, 1280, 128, None, {"linear": True}),
+    "items_128_odd_ring": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 224, 16384, 128, 2, {}),
+    "items_128_odd_ring_odd_k": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 160, 16384, 128, 3, {"ring": 3, "e_ring": 2}),
     "linear_odd_k": (RAGGED, 96, 256, 256, None, {"linear": True}),      # stays whole
 }
 
