@@ -155,7 +155,7 @@ def trace(args):
     lines += ["Template arguments: <mode, instrumented> (mode 0 = barrier-free, 1 = barrier); "
               "MoE: <phase, mode, instrumented>.  `gemm_part` / `gemm_mixed` <rows, columns of a part> and "
               "`moe_many` / `moe_part` / `moe_small` <phase, rows of a unit> are barrier-free; "
-              "`interp_kernel` <mode, instrumented, program in registers> is the generic interpreter.", "",
+              "`interp_kernel` <mode, instrumented, program in registers, inner loops without dispatch> is the generic interpreter.", "",
               "| Kernel | Calls | Average ns | Min ns | Max ns |", "|---|---|---|---|---|"]
     stems = [t for ts in STEMS.values() for t in ts] + ["interp_kernel"]
     for r in rows:
