@@ -214,6 +214,7 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
   // change of it empties the queue first.
   uint64_t queue = 0;
   uint32_t pending = 0, ops = 1;
+  uint32_t in_flight_pc = ~0u;             // instruction whose accesses the whole queue holds (~0: of several)
   auto add_slot = [&](uint32_t slot1) __attribute__((always_inline)) {
     if (slot1 != 0u) lds_add(counter(slot1 - 1u), 1u);
   };
@@ -232,6 +233,7 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
   auto issued = [&](uint32_t slot1) __attribute__((always_inline)) {      // one more instruction of `ops` accesses is in flight
     queue |= (uint64_t)slot1 << (8u * pending);
     pending += 1;
+    in_flight_pc = ~0u;
     if (kInstr) retire_all();
     else if (pending == kMaxPending || (pending + 1u) * ops > 16u) retire_one();
   };
@@ -364,13 +366,17 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
     uint32_t r = rl(rv, l), n = rl(tv, l);               // r of the trip's first iteration
     uint32_t ra = rl(rv, a), ha = rl(hv, a);
     const uint32_t ta = F.nest ? rl(tv, a) : ha;
-    // what is in flight is this instruction's, so that the queue is a count
-    // (a sum: a choice between captured variables would keep all of them in
-    // scratch memory)
+    // What is in flight from here on is this instruction's, so that the queue
+    // is a count.  (Told by the instruction, not by the queue's counter slots:
+    // those of instructions that nothing waits for are alike, and a store must
+    // not read its slot before a load ahead of it has landed there.  n_ops is a
+    // sum: a choice between captured variables would keep all of them in
+    // scratch memory.)
     const uint32_t is_ld = F.op == 1u, is_st = F.op == 5u;
     const uint32_t n_ops = is_ld * ld_ops + is_st * st_ops + (1u - is_ld - is_st) * ops;
     const uint64_t same = (uint64_t)F.slot1 * 0x0101010101010101ull;
-    if (pending > 0 && (ops != n_ops || !tiles || queue != (same & ((1ull << (8u * (pending & 7u))) - 1ull)))) retire_all();
+    if (in_flight_pc != F.pc) retire_all();
+    in_flight_pc = F.pc;
     ops = n_ops;
     const uint32_t most = max(min(kMaxPending, 16u / ops), 1u) - 1u;   // in flight after an instruction
     auto signal = [&](uint32_t m) __attribute__((always_inline)) {
