@@ -495,6 +495,7 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
       if (F.a2 == (int32_t)a) s2 = s2 + 1u == F.a3 ? 0u : s2 + 1u;
       if (tiles && F.a6 == a) tile += (int64_t)T;
     }
+    if (kWhich == OTHER && F.op == 4u) drain_lds();      // a load into the slot (direct to LDS) may follow
     if (F.n_waits > 0u && F.wait < 64u) seen = wl(seen, F.wait, x0.met);
     if (F.n_waits > 1u && F.wait + 1u < 64u) seen = wl(seen, F.wait + 1u, x1.met);
     if (pre_n > 0u && pre_wait < 64u) seen = wl(seen, pre_wait, y0.met);
@@ -641,6 +642,7 @@ __global__ void __launch_bounds__(512) interp_kernel(InterpParams P) {
       } else {
         retire_all();
         add_slot(slot1);
+        if (op == 4u) drain_lds();           // a load into the slot (direct to LDS) may follow
       }
       pc += 1;
       continue;

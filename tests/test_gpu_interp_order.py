@@ -1,6 +1,7 @@
 """Program order within one engine of the interpreter: an engine's load has
 landed before its next instruction reads the slot, whether or not anything
-waits for the load (an instruction that nothing waits for has no counter).
+waits for the load (an instruction that nothing waits for has no counter), and an
+add has written its slot before the next load goes there.
 Loads, stores and sums of one engine without dependencies between them, as an
 instruction before an inner loop and as sibling inner loops, with loads and
 stores of the same and of different widths (one buffer aligned, the other not)."""
@@ -14,7 +15,7 @@ torch = pytest.importorskip("torch")
 from oracle import core  # noqa: E402
 from paper_2608_13757_amd import ALLOC_PER_INSTR, ALLOC_PER_LOOP, MODE_BARRIER, MODE_BARRIER_FREE, Plan, bfs  # noqa: E402
 from tests.gpu_util import dev, trip_tensors  # noqa: E402
-from workloads import (OP_LOAD, OP_SCALE_ACC, OP_STORE_ACC, OP_STORE_RING, ProgramBuilder, TripTables,  # noqa: E402
+from workloads import (OP_ADDC, OP_LOAD, OP_SCALE_ACC, OP_STORE_ACC, OP_STORE_RING, ProgramBuilder, TripTables,  # noqa: E402
                        draw_trips, tile_args, tile_bases)
 
 PER, GEN = 3, 2
@@ -44,6 +45,46 @@ def order_program(form, tile, dep):
     p = b.build()
     p.tile_elems, p.ring_slots, p.n_accs = tile, [n], 1
     return p
+
+
+def overwrite_program(inner, tile):
+    """One engine over A{ LOAD r0; ADD r0 -> r1 (alone or in a loop C); LOAD r1;
+    STORE r1 }: the second load replaces what the add wrote."""
+    b = ProgramBuilder("interp", n_engines=1)
+    with b.loop("A") as A:
+        slot = dict(gen_loop=A, n_gen=GEN)
+        b.instr(0, OP_LOAD, tile_args(src=1, dst=0, idx_loop=A, **slot), name="LOAD0")
+        if inner:
+            with b.loop("C"):
+                b.instr(0, OP_ADDC, tile_args(src=0, dst=1, const=1.0, **slot), name="ADD")
+        else:
+            b.instr(0, OP_ADDC, tile_args(src=0, dst=1, const=1.0, **slot), name="ADD")
+        b.instr(0, OP_LOAD, tile_args(src=1, dst=1, idx_loop=A, **slot), name="LOAD1")
+        b.instr(0, OP_STORE_RING, tile_args(src=1, dst=2, idx_loop=A, **slot), name="STORE")
+    p = b.build()
+    p.tile_elems, p.ring_slots = tile, [GEN, GEN]
+    return p
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("inner", [False, True])
+@pytest.mark.parametrize("tile", [64, 256])
+def test_interp_load_after_add(tile, inner):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    bfs.lib()
+    n_wg, n_a = 64, 40
+    prog = overwrite_program(inner, tile)
+    tt = TripTables([draw_trips(prog, lambda l, n: np.full(n, n_a) if l == 1 else np.arange(n) % 3)] * n_wg)
+    base = n_a * np.arange(n_wg, dtype=np.int64)
+    x = torch.randn(n_wg * n_a * tile, generator=torch.Generator(device="cuda").manual_seed(tile), device="cuda")
+    out = torch.zeros_like(x)
+    t_dev, o_dev = trip_tensors(tt)
+    print(f"[interp order] overwrite tile={tile} inner={inner}", file=sys.stderr, flush=True)
+    plan = Plan(prog)
+    plan.run([dev(base), x, out], t_dev, o_dev, n_wg, watchdog_polls=20_000_000)
+    plan.status()
+    assert torch.equal(out, x)
 
 
 def order_trips(prog, form, n_wg, n_a):
