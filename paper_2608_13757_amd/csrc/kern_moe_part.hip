@@ -480,7 +480,8 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
   uint32_t total = 0;
   for (int c = 0; c < n_x; c += 64) {       // every wave counts, the first one writes
     const int i = c + (int)lane_id(), item = 8 * i + x;
-    uint32_t upto = 0;
+    uint32_t upto = 0, max_m = 0;
+    bool over = false;                      // a trip beyond the expert's M-tiles
     u32x4 w{}, v{};
     if (i < n_x && item < D.n_wg) {
       const int32_t e = P.work[4 * item], n0 = P.work[4 * item + 1], mt0 = P.work[4 * item + 2];
@@ -488,8 +489,18 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
       const int32_t e_lo = P.eoff[e], e_cnt = P.eoff[e + 1] - e_lo, left = e_cnt - mt0 * D.bm;
       const uint32_t rows = left <= 0 ? 0u : trip_m > (uint32_t)left / (uint32_t)D.bm ? (uint32_t)left : trip_m * (uint32_t)D.bm;
       upto = (rows + kPM - 1u) / kPM;
+      max_m = (uint32_t)(max(left, 0) + D.bm - 1) / (uint32_t)D.bm;
+      over = trip_m > max_m;
       w = u32x4{(uint32_t)e, (uint32_t)n0, (uint32_t)mt0, (uint32_t)e_lo};
       v = u32x4{(uint32_t)e_cnt, trip_m, 0u, 0u};
+    }
+    // Reported here, once on each XCD: an item without rows has no unit to
+    // report it.
+    const uint64_t bad = __ballot(over);
+    if (bad != 0ull && blockIdx.x < 8u && threadIdx.x < 64u) {
+      const int at = __builtin_ctzll(bad);
+      report_input(P.sc.err, 1u, (uint32_t)(8 * (c + at) + x), 1u, (uint32_t)__builtin_amdgcn_readlane((int)v.y, at),
+                   (uint32_t)__builtin_amdgcn_readlane((int)max_m, at), 0u);
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {      // inclusive sums

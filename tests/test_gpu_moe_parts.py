@@ -3,14 +3,17 @@ against the same program instrumented, which runs whole items one step at a
 time: every element has the same order of K in both, so the outputs are equal
 bit for bit.  (The instrumented run against the fp64 oracle is
 test_gpu_moe.py's.)"""
+import sys
+
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2608_13757_amd import ALLOC_PER_INSTR, ALLOC_PER_LOOP, MODE_BARRIER_FREE, Plan, bfs  # noqa: E402
+from paper_2608_13757_amd import ALLOC_PER_INSTR, ALLOC_PER_LOOP, MODE_BARRIER_FREE, BfsError, Plan, bfs  # noqa: E402
 from tests.gpu_util import trip_tensors  # noqa: E402
 from workloads import moe_program, moe_worklist  # noqa: E402
+from workloads.configs import moe_chunks  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +80,47 @@ def test_moe_units_equal_items(case, phase, alloc):
         outs.append(out)
     assert torch.isfinite(outs[1].view(torch.bfloat16).float()).all()
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("instrumented", [False, True])
+@pytest.mark.parametrize("phase", [1, 2])
+@pytest.mark.parametrize("case", ["quarters", "split", "items", "items_128_odd_ring", "items_phases"])
+@pytest.mark.parametrize("expert_rows", ["none", "some"])
+def test_moe_trip_beyond_rows_is_reported(case, phase, instrumented, expert_rows):
+    """An item whose M loop runs beyond its expert's M-tiles, without rows (no
+    unit of it runs) or with some, is reported by every kernel, at the ends of
+    the item list and inside."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    bfs.lib()
+    counts, k, n, bm, mchunk, opt = CASES[case]
+    tokens = sum(counts)
+    hidden, ffn = (k, n) if phase == 1 else (n, k)
+    perm = torch.arange(tokens, dtype=torch.int32, device="cuda")
+    eoff = torch.tensor(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32), device="cuda")
+    wl = moe_worklist(counts, phase, hidden, ffn, mchunk=mchunk, bm=bm)
+    trips, toff = wl.trips.flat()
+    plan = Plan(moe_program(phase, hidden, ffn, bm=bm, **opt))
+    ins = [perm, eoff] + [torch.zeros(s, dtype=torch.bfloat16, device="cuda")
+                          for s in [(tokens, k)] + [(len(counts), n, k)] * (2 if phase == 1 else 1)]
+    out = torch.zeros((tokens, n), dtype=torch.bfloat16, device="cuda")
+    n_wg = wl.trips.n_wg
+    stats = torch.zeros(n_wg * plan.n_waves * 8, dtype=torch.int64, device="cuda") if instrumented else None
+    expert = counts.index(0) if expert_rows == "none" else counts.index(max(counts))
+    limit = -(-counts[expert] // bm)
+    for at in (0, n_wg // 2 + 3, n_wg - 1):
+        work, t = wl.work.copy(), trips.copy()
+        work[at] = (expert, 0, 0, limit + 1)
+        # an own table behind the others: M beyond the rows, K and C for these M-tiles
+        tables = np.r_[[limit + 1], np.full(limit + 1, k // 32), np.full(limit + 1, moe_chunks(phase, bm))]
+        off = toff.copy()
+        off[at, 1:] = len(t) + np.array([0, 1, 1 + limit + 1])
+        args = [torch.from_numpy(work.reshape(-1)).cuda()] + ins + [out]
+        dev = [torch.from_numpy(a).cuda() for a in (np.r_[t, tables.astype(np.int32)], off)]
+        print(f"[moe trips] {case} phase={phase} rows={expert_rows} instrumented={instrumented} item {at} of {n_wg}",
+              file=sys.stderr, flush=True)
+        plan.run(args, dev[0], dev[1], n_wg, stats=stats)
+        with pytest.raises(BfsError) as e:
+            plan.status()
+        assert e.value.status == bfs.E_INVALID
+        plan.status()                          # reported once
