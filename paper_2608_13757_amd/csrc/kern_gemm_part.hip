@@ -398,6 +398,11 @@ __global__ void __launch_bounds__(768) gemm_mixed_kernel(GemmParams P) {
 bool bfsgemm::launch_parts(GemmParams &P, int n_wg, hipStream_t s, bfs_status &st) {
   constexpr int kCUs = 256;
   if (P.ring % 2 != 0) return false;       // the ring is used in pairs of slots
+  // A pair of loads waits for what its second step does, so that must not be an
+  // MMA of the pair itself: an offset of 1 leaves one step in flight (K step by
+  // K step instead).
+  for (int j = 0; j < P.load.n; ++j)
+    if ((P.load.w[j].w.w2 & 0xffffu) < 2u) return false;
   // SPILL's waits on loops outside C are constant during its trip
   InstrWaits once = P.spill, chunk = P.spill;
   once.n = chunk.n = 0;

@@ -24,12 +24,20 @@ def _gpu():
     bfs.lib()
 
 
-def _run(m, n, k, ring, e_ring, steps, chunks):
+def _program(m, n, k, ring, e_ring, offset=None):
+    """offset: of MMA->LOAD in place of the ring's depth."""
+    p = gemm_program(m, n, k, ring=ring, e_ring=e_ring)
+    reuse = (p.instr_id("MMA"), p.instr_id("LOAD"))
+    p.deps = [(a, c, offset if offset and (a, c) == reuse else o) for a, c, o in p.deps]
+    return p
+
+
+def _run(m, n, k, ring, e_ring, steps, chunks, offset=None):
     g = torch.Generator(device="cuda").manual_seed(m + n + k)
     a = torch.randn((m, k), generator=g, device="cuda").bfloat16()
     bt = torch.randn((n, k), generator=g, device="cuda").bfloat16()
     bias = torch.randn((n,), generator=g, device="cuda")
-    plan = Plan(gemm_program(m, n, k, ring=ring, e_ring=e_ring))
+    plan = Plan(_program(m, n, k, ring, e_ring, offset))
     trips, off = trip_tensors(gemm_trips(m, n, k))
     if steps is not None:
         trips[off[:, 1]] = steps
@@ -38,10 +46,10 @@ def _run(m, n, k, ring, e_ring, steps, chunks):
     n_wg = (m // 256) * (n // 256)
     outs = []
     for stats in (None, torch.zeros(n_wg * plan.n_waves * 8, dtype=torch.int64, device="cuda")):
-        print(f"[gemm-parts] {m}x{n}x{k} ring={ring} e_ring={e_ring} steps={steps} chunks={chunks} "
+        print(f"[gemm-parts] {m}x{n}x{k} ring={ring} e_ring={e_ring} steps={steps} chunks={chunks} offset={offset} "
               f"stats={stats is not None}", file=sys.stderr, flush=True)
         c = torch.full((m, n), -1.0, dtype=torch.bfloat16, device="cuda")
-        plan.run([a, bt, bias, c], trips, off, n_wg, stats=stats)
+        plan.run([a, bt, bias, c], trips, off, n_wg, stats=stats, watchdog_polls=20_000_000)
         plan.status()
         outs.append(c)
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
@@ -67,6 +75,15 @@ def test_gemm_grids(tm, tn, k):
 @pytest.mark.parametrize("tm,tn", [(2, 3), (9, 11), (2, 150)])
 def test_gemm_rings(tm, tn, ring, e_ring):
     _run(256 * tm, 256 * tn, 288, ring, e_ring, None, None)
+
+
+@pytest.mark.parametrize("ring,offset", [(2, 1), (3, 1), (3, 2), (4, 1), (4, 2), (4, 3)])
+@pytest.mark.parametrize("tm,tn,k", [(2, 3, 32), (2, 3, 288), (9, 11, 320), (2, 150, 160)])
+def test_gemm_smaller_offsets(tm, tn, k, ring, offset):
+    """Programs that reuse a ring slot later than they could: LOAD waits for the
+    MMA 1, 2 or 3 steps back.  (With 1 a load waits for the MMA before it, so
+    steps cannot go in pairs.)"""
+    _run(256 * tm, 256 * tn, k, ring, 1, None, None, offset)
 
 
 @pytest.mark.parametrize("steps,chunks", [(0, 8), (1, 8), (4, 3), (5, 0), (7, 5)])
