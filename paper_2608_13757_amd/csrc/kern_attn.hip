@@ -732,6 +732,10 @@ bfs_status launch_attn(const bfs_plan *p, DevImage *img, const void *const *bufs
   }
   P.pread_pv = P.pread;
   for (int j = 0; j < P.pv.n && P.pread_pv.n < kMaxWaits; ++j) P.pread_pv.w[P.pread_pv.n++] = P.pv.w[j];
+  // A program whose V load waits for the same step's PREAD cannot have PREAD
+  // wait for that load: it runs on the kernel that waits per instruction (the
+  // instrumented one).
+  const bool apart = has_dep(p, pr, lv, 0);
   P.sc = sync_common(img, dbg, dbg_cap, o, kWaves);
   P.work = static_cast<const int32_t *>(bufs[0]);
   P.q = static_cast<const __bf16 *>(bufs[1]);
@@ -745,7 +749,7 @@ bfs_status launch_attn(const bfs_plan *p, DevImage *img, const void *const *bufs
   P.nv = nv;
   P.desc_cap = desc_cap;
   P.scale_log2 = 1.4426950408889634f / 11.313708498984761f;   // log2(e) / sqrt(128)
-  const bool instr = dbg || o.dev_stats || o.fault_dep >= 0;
+  const bool instr = dbg || o.dev_stats || o.fault_dep >= 0 || (apart && p->mode == BFS_MODE_BARRIER_FREE);
   hipStream_t s = (hipStream_t)stream;
   auto go = [&](auto kern) -> bfs_status {
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -18,11 +18,7 @@ pytestmark = pytest.mark.gpu
 RAGGED = [1, 63, 64, 65, 127, 128, 129, 200, 321, 777]
 
 
-@pytest.mark.parametrize("alloc", [ALLOC_PER_LOOP, ALLOC_PER_INSTR])
-@pytest.mark.parametrize("linear", [False, True])
-@pytest.mark.parametrize("rings", [(2, 2), (2, 3), (3, 2)])
-@pytest.mark.parametrize("lengths,heads,n_wg", [(RAGGED, 2, 256), (RAGGED, 3, 5), ([1], 1, 8), ([2000], 1, 1)])
-def test_attn_lean_equals_instrumented(lengths, heads, n_wg, rings, linear, alloc):
+def _compare(program, lengths, heads, n_wg, alloc):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     bfs.lib()
@@ -32,7 +28,7 @@ def test_attn_lean_equals_instrumented(lengths, heads, n_wg, rings, linear, allo
     wl = attn_worklist(np.array(lengths), heads, n_wg=n_wg)
     trips, toff = trip_tensors(wl.trips)
     work = torch.from_numpy(wl.work.reshape(-1)).cuda()
-    plan = Plan(attn_program(heads, nk=rings[0], nv=rings[1], linear=linear), MODE_BARRIER_FREE, alloc)
+    plan = Plan(program, MODE_BARRIER_FREE, alloc)
     outs = []
     for cap in (0, 4):
         out = torch.full((tokens, heads, 128), -1, dtype=torch.int16, device="cuda")
@@ -43,3 +39,31 @@ def test_attn_lean_equals_instrumented(lengths, heads, n_wg, rings, linear, allo
         outs.append(out)
     assert torch.isfinite(outs[1].view(torch.bfloat16).float()).all()
     assert torch.equal(outs[0], outs[1])
+    return outs[0]
+
+
+@pytest.mark.parametrize("alloc", [ALLOC_PER_LOOP, ALLOC_PER_INSTR])
+@pytest.mark.parametrize("linear", [False, True])
+@pytest.mark.parametrize("rings", [(2, 2), (2, 3), (3, 2)])
+@pytest.mark.parametrize("lengths,heads,n_wg", [(RAGGED, 2, 256), (RAGGED, 3, 5), ([1], 1, 8), ([2000], 1, 1)])
+def test_attn_lean_equals_instrumented(lengths, heads, n_wg, rings, linear, alloc):
+    _compare(attn_program(heads, nk=rings[0], nv=rings[1], linear=linear), lengths, heads, n_wg, alloc)
+
+
+@pytest.mark.parametrize("alloc", [ALLOC_PER_LOOP, ALLOC_PER_INSTR])
+@pytest.mark.parametrize("linear", [False, True])
+@pytest.mark.parametrize("lengths,heads,n_wg", [(RAGGED, 3, 5), ([1], 1, 8)])
+def test_attn_v_load_after_pread(lengths, heads, n_wg, linear, alloc):
+    """A program whose V load waits for the step's PREAD, so that PREAD cannot
+    wait with PV: the same bits as the program without that wait."""
+    p = attn_program(heads, linear=linear)
+    kv = next(b for b in p.blocks if p.instr_id("LOADV") in b)
+    kv.insert(kv.index(p.instr_id("PREAD")), kv.pop(kv.index(p.instr_id("LOADV"))))
+    order = [i for b in p.blocks for i in b]
+    new = {old: i for i, old in enumerate(order)}
+    p.instrs = [p.instrs[i] for i in order]
+    p.blocks = [[new[i] for i in b] for b in p.blocks]
+    p.deps = [(new[a], new[c], k) for a, c, k in p.deps] + [(p.instr_id("PREAD"), p.instr_id("LOADV"), 0)]
+    p.dep_linear = p.dep_linear + [0]
+    out = _compare(p, lengths, heads, n_wg, alloc)
+    assert torch.equal(out, _compare(attn_program(heads, linear=linear), lengths, heads, n_wg, alloc))
