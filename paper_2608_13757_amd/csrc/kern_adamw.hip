@@ -40,6 +40,8 @@ using namespace bfsdev;
 
 namespace {
 
+constexpr int64_t kPlainFrom = 40 << 20, kPlainTo = 256 << 20;     // bytes of p, g, m and v
+
 struct AdamParams {
   SyncCommon sc;
   InstrWaits load, upd, store;
@@ -56,7 +58,8 @@ struct AdamParams {
   uint32_t slot_bytes;
 };
 
-template <int kMode, bool kInstr>
+// kPlain: stores that stay in the caches (see the launch for where).
+template <int kMode, bool kInstr, bool kPlain>
 __global__ void __launch_bounds__(64 * 6) adamw_kernel(AdamParams P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   uint32_t *cnt = reinterpret_cast<uint32_t *>(lds);
@@ -88,8 +91,10 @@ __global__ void __launch_bounds__(64 * 6) adamw_kernel(AdamParams P) {
   };
   // A launch of one or two chunks per workgroup is a chain of latencies (trip
   // offset, trip, chunk, stores): barrier-free, the first chunk (its slot is
-  // free) is loaded before the trip is known and the counters are cleared
-  // (one chunk: 6.9 to 6.7 us per launch, 2^20 parameters: 9.55 to 9.4).
+  // free) is loaded before the trip is known and the counters are cleared.  (us
+  // without and with: 2^18 parameters, a chunk per workgroup, 7.6 and 7.3; 2^20,
+  // two chunks, 9.4 and 9.3; 3 * 2^20 17.2 and 16.5, 2^22 22.6 and 21.9; with the
+  // caches full of other data 2^20 19.4 and 18.1.)
   constexpr bool kAhead = kMode != BFS_MODE_BARRIER && !kInstr;
   const bool ahead = kAhead && c0 >= 0 && c0 < n_chunks;
   if (ahead && wave == 0) load_chunk(c0, ring);
@@ -194,8 +199,11 @@ __global__ void __launch_bounds__(64 * 6) adamw_kernel(AdamParams P) {
           for (uint32_t b = 0; b < blocks; ++b) {
             const int64_t e = e0 + 256 * (int64_t)b + 4 * (int64_t)lane;
             const f32x4 d = *(const BFS_LDS f32x4 *)(uintptr_t)(base + part[a] * CH * 4u + 1024u * b);
-            // (plain stores: 3 * 2^20 parameters 16.4 us, nontemporal 17.3; 2^27 alike)
-            if (e < P.n) *reinterpret_cast<f32x4 *>(dst[a] + e) = d;
+            f32x4 *to = reinterpret_cast<f32x4 *>(dst[a] + e);
+            if (e < P.n) {
+              if constexpr (kPlain) *to = d;
+              else __builtin_nontemporal_store(d, to);
+            }
           }
         }
       }
@@ -289,8 +297,16 @@ bfs_status launch_adamw(const bfs_plan *p, DevImage *img, const void *const *buf
     return BFS_OK;
   };
   if (p->mode == BFS_MODE_BARRIER)
-    return instr ? go(adamw_kernel<BFS_MODE_BARRIER, true>) : go(adamw_kernel<BFS_MODE_BARRIER, false>);
-  return instr ? go(adamw_kernel<BFS_MODE_BARRIER_FREE, true>) : go(adamw_kernel<BFS_MODE_BARRIER_FREE, false>);
+    return instr ? go(adamw_kernel<BFS_MODE_BARRIER, true, false>) : go(adamw_kernel<BFS_MODE_BARRIER, false, false>);
+  if (instr) return go(adamw_kernel<BFS_MODE_BARRIER_FREE, true, false>);
+  // Plain stores where p, g, m and v fit the 256 MiB last-level cache but not,
+  // by some margin, the L2s (32 MiB): the next launch on them finds the results
+  // there.  Beyond, they push out what that launch reads.  (us with nontemporal
+  // and with plain stores: 2.07 M parameters 10.6 and 11.1, 2.2 M 12.9 and 13.2;
+  // 3.1 M 16.5 and 16.1, 4.2 M 21.9 and 21.0, 8.4 M 41.4 and 39.4; 20 M 89.6 and
+  // 91.3, 33.8 M 186 and 204.  With the caches full of other data alike.)
+  return N * 16 > kPlainFrom && N * 16 <= kPlainTo ? go(adamw_kernel<BFS_MODE_BARRIER_FREE, false, true>)
+                                                  : go(adamw_kernel<BFS_MODE_BARRIER_FREE, false, false>);
 }
 
 }  // namespace bfs

@@ -42,7 +42,7 @@ KERNELS = {
              ["gemm_part_kernel<256, 256>"]),
     "attn": (["kern_attn.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["attn_kernel<0, false>"]),
     "rms": (["kern_rms.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["rms_kernel<0, false, 4>"]),
-    "adamw": (["kern_adamw.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["adamw_kernel<0, false>"]),
+    "adamw": (["kern_adamw.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["adamw_kernel<0, false, false>"]),
     "moe": (["kern_moe.hip", "kern_moe_part.hip", "moe_common.h", "engine_sync.h", "device_sync.h", "bfs_internal.h"],
             ["moe_many_kernel<1, 256>", "moe_many_kernel<2, 256>"]),
     "chain": (["kern_chain.hip", "engine_sync.h", "device_sync.h", "bfs_internal.h"], ["chain_kernel<0, false>"]),
@@ -153,7 +153,7 @@ def trace(args):
     for c in args.command:
         lines += ["```", c, "```", ""]
     lines += ["Template arguments: <mode, instrumented> (mode 0 = barrier-free, 1 = barrier); "
-              "MoE: <phase, mode, instrumented>.  `gemm_part` / `gemm_mixed` <rows, columns of a part> and "
+              "MoE: <phase, mode, instrumented>, AdamW: <mode, instrumented, plain stores>.  `gemm_part` / `gemm_mixed` <rows, columns of a part> and "
               "`moe_many` / `moe_part` / `moe_small` <phase, rows of a unit> are barrier-free; "
               "`interp_kernel` <mode, instrumented, program in registers, inner loops without dispatch> is the generic interpreter.", "",
               "| Kernel | Calls | Average ns | Min ns | Max ns |", "|---|---|---|---|---|"]

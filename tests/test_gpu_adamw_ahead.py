@@ -9,7 +9,7 @@ torch = pytest.importorskip("torch")
 
 from paper_2608_13757_amd import MODE_BARRIER_FREE, Plan, bfs  # noqa: E402
 from tests.gpu_util import trip_tensors  # noqa: E402
-from workloads import adamw_program, adamw_worklist  # noqa: E402
+from workloads import adamw_default_wg, adamw_program, adamw_worklist  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,10 @@ def test_adamw_ahead_equals_instrumented(n, chunk, n_wg, ring):
         outs.append((p, m, v))
     for a, b in zip(*outs):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [(40 << 16) + 4, 1 << 24, (40 << 16), (1 << 24) + 4])
+def test_adamw_store_kinds_equal_instrumented(n):
+    """Vectors just inside and just outside the sizes whose results are stored
+    through the caches: the same bits as the instrumented launch."""
+    test_adamw_ahead_equals_instrumented(n, 1024, adamw_default_wg(n, 1024), 2)
