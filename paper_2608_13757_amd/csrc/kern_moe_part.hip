@@ -480,8 +480,7 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
   uint32_t total = 0;
   for (int c = 0; c < n_x; c += 64) {       // every wave counts, the first one writes
     const int i = c + (int)lane_id(), item = 8 * i + x;
-    uint32_t upto = 0, max_m = 0;
-    bool over = false;                      // a trip beyond the expert's M-tiles
+    uint32_t upto = 0;
     u32x4 w{}, v{};
     if (i < n_x && item < D.n_wg) {
       const int32_t e = P.work[4 * item], n0 = P.work[4 * item + 1], mt0 = P.work[4 * item + 2];
@@ -489,18 +488,8 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
       const int32_t e_lo = P.eoff[e], e_cnt = P.eoff[e + 1] - e_lo, left = e_cnt - mt0 * D.bm;
       const uint32_t rows = left <= 0 ? 0u : trip_m > (uint32_t)left / (uint32_t)D.bm ? (uint32_t)left : trip_m * (uint32_t)D.bm;
       upto = (rows + kPM - 1u) / kPM;
-      max_m = (uint32_t)(max(left, 0) + D.bm - 1) / (uint32_t)D.bm;
-      over = trip_m > max_m;
       w = u32x4{(uint32_t)e, (uint32_t)n0, (uint32_t)mt0, (uint32_t)e_lo};
       v = u32x4{(uint32_t)e_cnt, trip_m, 0u, 0u};
-    }
-    // Reported here, once on each XCD: an item without rows has no unit to
-    // report it.
-    const uint64_t bad = __ballot(over);
-    if (bad != 0ull && blockIdx.x < 8u && threadIdx.x < 64u) {
-      const int at = __builtin_ctzll(bad);
-      report_input(P.sc.err, 1u, (uint32_t)(8 * (c + at) + x), 1u, (uint32_t)__builtin_amdgcn_readlane((int)v.y, at),
-                   (uint32_t)__builtin_amdgcn_readlane((int)max_m, at), 0u);
     }
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {      // inclusive sums
@@ -533,6 +522,21 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
                  (int32_t)uniform(v.x), uniform(v.y)};
     run_units<kPhase, kPM, 256>(P, D, lds, 8 * at + x, (int)(unit - before), I);
   }
+  // Trips beyond the expert's M-tiles, once on each XCD: an item without rows has
+  // no unit that would report them.
+  if (blockIdx.x < 8u && threadIdx.x < 64u) {
+    for (int c0 = 0; c0 < n_x; c0 += 64) {
+      const int i = min(c0 + (int)lane_id(), n_x - 1);
+      const u32x4 w = *(const BFS_LDS u32x4 *)(uintptr_t)(table + 32u * (uint32_t)i);
+      const u32x4 v = *(const BFS_LDS u32x4 *)(uintptr_t)(table + 32u * (uint32_t)i + 16u);
+      const uint32_t max_m = (uint32_t)(max((int32_t)v.x - (int32_t)w.z * D.bm, 0) + D.bm - 1) / (uint32_t)D.bm;
+      const uint64_t bad = __ballot(v.y > max_m);
+      if (bad == 0ull) continue;
+      const int at = __builtin_ctzll(bad);
+      report_input(P.sc.err, 1u, (uint32_t)(8 * (c0 + at) + x), 1u, (uint32_t)__builtin_amdgcn_readlane((int)v.y, at),
+                   (uint32_t)__builtin_amdgcn_readlane((int)max_m, at), 0u);
+    }
+  }
 }
 
 // At most kScan items: in quarters of 128 x 128 if these fit the compute units
@@ -543,22 +547,24 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
 // both phases 50 us, so 35).  (us of phase 1 and 2 in whole units, in quarters:
 // 8 experts of 128 rows, K = 2048 and 1408, 176 and 128 quarters, 43 and 33, 33
 // and 25; 2048 ragged rows, K = 1024 and 1408, 440 and 160 quarters, 31 and 39,
-// 38 and 25.)
+// 38 and 25.)  The workgroup's item comes out of the counting lanes' registers:
+// read from memory again it cost 1.5 us (128 items of a few rows, K = 256: 12.7
+// us, so 11.2; whole items without a count 9.8).
 constexpr int kScan = 128, kCUs = 256;
 
 template <int kPhase, int kPM>
 __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   // (both halves' loads first: two levels deep, from cold lines)
-  int32_t mt0[kScan / 64], lo[kScan / 64], hi[kScan / 64];
+  int32_t e[kScan / 64], n0[kScan / 64], mt0[kScan / 64], lo[kScan / 64], hi[kScan / 64];
   uint32_t trip[kScan / 64];
   {
-    int32_t e[kScan / 64];
     int64_t at[kScan / 64];
 #pragma unroll
     for (int h = 0; h < kScan / 64; ++h) {
       const int i = min(64 * h + (int)lane_id(), D.n_wg - 1);
       e[h] = P.work[4 * i];
+      n0[h] = P.work[4 * i + 1];
       mt0[h] = P.work[4 * i + 2];
       at[h] = P.trip_off[(int64_t)i * 4 + 1];
     }
@@ -593,6 +599,7 @@ __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
     if (blockIdx.x / 8u >= per || q >= quarters) return;
     int wg = 0;
     uint32_t sub = 0, parts = 2;
+    Item I{};
 #pragma unroll
     for (int h = kScan / 64 - 1; h >= 0; --h) {
       const uint64_t above = __ballot(upto[h] > q);
@@ -601,12 +608,14 @@ __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
         wg = 64 * h + at;
         parts = uniform(__shfl(own[h], at));
         sub = q - (uniform(__shfl(upto[h], at)) - parts);
+        auto of = [&](int32_t v) { return __builtin_amdgcn_readlane(v, at); };
+        I = Item{of(e[h]), of(n0[h]), of(mt0[h]), of(lo[h]), of(hi[h]) - of(lo[h]), (uint32_t)of((int32_t)trip[h])};
       }
     }
     Split Q = D;
     Q.sm = (int32_t)(parts / 2u);
     Q.sn = 2;
-    run_units<kPhase, 128, 128>(P, Q, lds, wg, (int)sub, read_item(P, wg));
+    run_units<kPhase, 128, 128>(P, Q, lds, wg, (int)sub, I);
     return;
   }
   const int wg = blockIdx.x % D.items, sub = blockIdx.x / D.items;
