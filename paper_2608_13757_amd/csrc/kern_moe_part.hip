@@ -635,6 +635,18 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
   // M-tiles, where a single last step would break the twos.
   const int slots = P.ring & ~1, ksteps = P.kdim / kBK;
   if (linear && ksteps % 2 != 0) return false;
+  // Whole items stay where units do not win back what they cost.  (Time of whole
+  // items over units, the geometric mean of calls of mixed expert sizes and, in
+  // brackets, the range: within it the rows per expert decide, which the host
+  // does not know.)
+  //   One pair of slots, from a ring of three: 129 .. 192 items 1.15 (0.76 ..
+  //   2.6), 193 .. 768 items 0.95 (0.66 .. 1.8).
+  //   M-tiles of 128 rows, more than 384 items: phase 1, K <= 512, 0.94 (0.80 ..
+  //   1.14), above 1.07; phase 2, K <= 256, 0.98 (0.78 .. 1.08), above 1.03.  Up
+  //   to 384 items 1.0 .. 1.4 over every range of K (0.74 .. 3.4).
+  //   M-tiles of 256 rows: 1.05 .. 2 over every range (0.89 .. 3.5).
+  if (P.ring == 3 && n_wg > 192) return false;
+  if (bm == 128 && n_wg > 384 && P.kdim <= (phase == 1 ? 512 : 256)) return false;
   auto go = [&](auto part, auto many, auto small, auto unit) -> bool {
     using G = decltype(unit);
     const int chunks = phase == 1 ? G::kRB : 2 * G::kRB;
@@ -642,13 +654,15 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
     const size_t base = kCntBytes + ring + (size_t)P.e_ring * kESlotBytes;
     // Up to four workgroups for an item's units (runs of four M-tiles) while
     // the items are few; beyond `few` of them, workgroups that stay and take the
-    // units in turn.  Phase 1 gains from its first grid of more than a round of
-    // units (us split and in turn, items in brackets): [224] 145 and 109, [248]
-    // 413 and 363, [304] 483 and 448, [352] 770 and 824, [376] 117 and 129,
-    // [448] 88 and 67, [1040] 1048 and 951 (a workgroup per item).  Phase 2's
-    // units are shorter and store twice the chunks: [176] 44 and 48, [312] 214
-    // and 220, [448] 254 and 233, [512] 390 and 417, [720] 349 and 254, [1520]
-    // 515 and 497.
+    // units in turn.  The rows per expert decide which is faster, and the host
+    // does not know them; the line is where it pays on average.  Phase 1, us split
+    // and in turn, items in brackets: [224] 145 and 109, [248] 413 and 363, [304]
+    // 483 and 448, [448] 88 and 67, [1040] 1048 and 951 (a workgroup per item),
+    // but [352] 770 and 824, [376] 117 and 129; 32 experts [352] of 16, 256, 512
+    // and 1024 rows each, K = 2048, 98 and 110, 139 and 144, 231 and 209, 448 and
+    // 383.  Phase 2's units are shorter and store twice the chunks: [176] 44 and
+    // 48, [312] 214 and 220, [448] 254 and 233, [512] 390 and 417, [720] 349 and
+    // 254, [1520] 515 and 497.
     const int few = phase == 1 ? kScan : 512;
     const int items = (n_wg + 7) / 8 * 8;
     const size_t table = (size_t)items / 8 * 32;

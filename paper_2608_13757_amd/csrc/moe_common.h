@@ -39,7 +39,7 @@ __device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcp
 // Barrier-free, uninstrumented launches: K steps in pairs, work items split where
 // the grid leaves compute units idle, row blocks past the expert's count left
 // out.  bm: the program's M-tile height; linear: MMA->LOAD read linearized.
-// False (nothing launched) if the rings do not allow it.
+// False (nothing launched) if the rings do not allow it or whole items are faster.
 bool launch_parts(const MoeParams &P, int phase, int bm, bool linear, int n_wg, hipStream_t s, bfs_status &st);
 
 }  // namespace bfsmoe

@@ -45,6 +45,10 @@ CASES = {
     "split_128_linear_odd_ring": ([1100, 900, 255, 257, 64, 1, 0, 700], 192, 1280, 128, None, {"linear": True}),
     "items_128_odd_ring": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 224, 16384, 128, 2, {}),
     "items_128_odd_ring_odd_k": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 160, 16384, 128, 3, {"ring": 3, "e_ring": 2}),
+    "items_128_long_k": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 576, 8192, 128, 2, {}),
+    "items_128_long_odd_k": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 544, 16384, 128, 3, {}),
+    "whole_128_short_k": ([40, 300, 0, 1, 257, 96, 31, 510, 32, 33], 256, 8192, 128, 2, {}),
+    "whole_odd_ring": ([1100, 900, 255, 257, 64, 1, 0, 700], 96, 6144, 256, 2, {"ring": 3, "e_ring": 1}),
     "linear_odd_k": (RAGGED, 96, 256, 256, None, {"linear": True}),      # stays whole
 }
 
