@@ -65,8 +65,8 @@ __device__ __forceinline__ uint32_t swz(uint32_t row, uint32_t chunk) {
 
 // Barrier-free, uninstrumented launches of the looped program: whole tiles or
 // parts of them, K steps in pairs.  False (nothing launched, P as it was) if the
-// ring's depth is odd, LOAD waits for the MMA before it, or SPILL's waits are not
-// of the program's usual kinds.
+// ring's depth is odd, LOAD waits for the MMA before it, SPILL's waits are not of
+// the program's usual kinds, or a ring of two slots does better step by step.
 bool launch_parts(GemmParams &P, int n_wg, hipStream_t s, bfs_status &st);
 
 }  // namespace bfsgemm

@@ -411,13 +411,19 @@ bool bfsgemm::launch_parts(GemmParams &P, int n_wg, hipStream_t s, bfs_status &s
     to.w[to.n++] = P.spill.w[j];
   }
   if (!bfs::no_dynamic(chunk) || !bfs::waits_fit({{&once, 3}, {&chunk, 1}})) return false;
-  P.spill_once = once;
-  P.spill = chunk;
   const int rest = n_wg % kCUs;
-  P.n_whole = n_wg - rest;
   int parts = rest == 0 ? 1 : 4 * rest <= kCUs ? 4 : 2 * rest <= kCUs ? 2 : 1;
   // halves: the epilogue slots in use must fit the smaller ring
   if (parts == 2 && (size_t)std::min(P.e_ring, 4) * kESlotBytes > (size_t)P.ring * Part<256, 128>::kSlot) parts = 1;
+  // A ring of two slots holds one pair, so that a whole tile's loads and MMAs
+  // take turns: single steps overlap.  (us step by step and in pairs, 256 tiles:
+  // K = 4096 139 and 151, 512 34 and 32, 96 23 and 19; 168 tiles, K = 4096, 120
+  // and 145; 128 tiles, not in halves as four epilogue slots do not fit there,
+  // K = 1024 43 and 46.)
+  if (P.ring == 2 && parts == 1 && P.k > 512) return false;
+  P.spill_once = once;
+  P.spill = chunk;
+  P.n_whole = n_wg - rest;
   auto go = [&](auto kern, uint32_t slot, int columns, int grid) {
     const size_t lds = kCntBytes + (size_t)P.ring * slot + 4 * columns;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -77,6 +77,14 @@ def test_gemm_rings(tm, tn, ring, e_ring):
     _run(256 * tm, 256 * tn, 288, ring, e_ring, None, None)
 
 
+@pytest.mark.parametrize("e_ring", [1, 4])
+@pytest.mark.parametrize("tm,tn,k", [(2, 3, 544), (9, 11, 512), (9, 11, 544), (12, 12, 512), (12, 12, 544), (5, 53, 544)])
+def test_gemm_ring_of_two(tm, tn, k, e_ring):
+    """One pair of slots: whole tiles in pairs up to K = 512, step by step beyond;
+    parts in pairs."""
+    _run(256 * tm, 256 * tn, k, 2, e_ring, None, None)
+
+
 @pytest.mark.parametrize("ring,offset", [(2, 1), (3, 1), (3, 2), (4, 1), (4, 2), (4, 3)])
 @pytest.mark.parametrize("tm,tn,k", [(2, 3, 32), (2, 3, 288), (9, 11, 320), (2, 150, 160)])
 def test_gemm_smaller_offsets(tm, tn, k, ring, offset):
