@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
 
 
 def _program(tile, slots, depth, acquire):
-    """Four engines over [O{] A{ [ACQ] B{ LOAD | ADD | ACC | STORE } } [}]."""
+    """Four engines over [O{] [ACQO] A{ [ACQ] B{ LOAD | ADD | ACC | STORE } } [}].
+    Slots by the position in B start over at each iteration of O too, where ACQ's
+    offset, counted per trip of A, does not reach back: ACQO drains them there."""
     b = ProgramBuilder("interp", n_engines=4)
 
     def nest():
@@ -42,6 +44,8 @@ def _program(tile, slots, depth, acquire):
 
     if depth == 3:
         with b.loop("O"):
+            if acquire and slots == "pos":
+                b.instr(0, OP_NOP, name="ACQO")
             n = nest()
     else:
         n = nest()
@@ -59,6 +63,9 @@ def _program(tile, slots, depth, acquire):
             b.dep("ADD", "ACQ", 1)
         b.dep("ACC", "ACQ", 1)
         b.dep("STORE", "ACQ", 1)
+        if depth == 3 and slots == "pos":
+            b.dep("ACC", "ACQO", 1)
+            b.dep("STORE", "ACQO", 1)
     p = b.build()
     p.tile_elems, p.ring_slots, p.n_accs = tile, [n, n], 1
     return p
