@@ -127,9 +127,6 @@ def _ptr(x):
     return x.data_ptr()
 
 
-_torch_C = None          # torch's binding module, once a device is in use
-
-
 def _ptr_array(buffers):
     """The buffers' addresses as a C array (packed bytes: a fifth of the time
     of a ctypes array)."""

@@ -489,8 +489,6 @@ struct Sync {
 
 namespace bfs {
 
-// Host: copy one instruction's waits (and its counter slot) into kernel
-// arguments.  False when the instruction has more waits than fit.
 // Host: true when loop x lies in the subtree of loop l (x == l included).
 inline bool in_subtree(const bfs_plan *p, int x, int l) {
   for (; x >= 0; x = p->loop_parent[x])

@@ -500,9 +500,12 @@ bfs_status launch_gemm(const bfs_plan *p, DevImage *img, const void *const *bufs
     if (e != hipSuccess) return fail(BFS_E_DEVICE, std::string("gemm launch: ") + hipGetErrorString(e));
     return BFS_OK;
   };
-  // Instrumented launches (debug log, statistics, injected faults) run the
-  // same unrolled bodies as timed ones, so the debug log records the waits
-  // of the code path that is timed.
+  // Instrumented launches (debug log, statistics, injected faults) run these
+  // bodies, the same as uninstrumented ones in barrier mode, with k_unroll 2, 4
+  // or 8 and of the K-unrolled program.  Uninstrumented barrier-free launches
+  // with k_unroll 1 mostly run in pairs of steps instead (launch_parts): a pair
+  // waits once, for the threshold that the log shows for its second step, and
+  // is compared by its outputs, which have the same bits.
   auto pick = [&](auto mode_tag, auto instr_tag) -> bfs_status {
     constexpr int kM = decltype(mode_tag)::value;
     constexpr bool kI = decltype(instr_tag)::value;

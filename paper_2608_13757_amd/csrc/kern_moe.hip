@@ -165,7 +165,6 @@ __global__ void __launch_bounds__(768) moe_kernel(MoeParams P) {
         if (tk != (int32_t)ksteps || tc != (int32_t)chunks)
           report_input(P.sc.err, 2u, (uint32_t)wg, mi, (uint32_t)tk, (uint32_t)tc, (uint32_t)wave);
       }
-      const int32_t m0 = (mt0 + (int32_t)mi) * kBM;
       // source rows of this M-tile as 32-bit per-lane byte offsets from a
       // wave-uniform base that advances one K step per iteration: the loads
       // take the scalar-base address form and need no vector address

@@ -544,7 +544,7 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
 // every wave counts them from the items' trips, and finds the workgroup's own
 // in the sums: a workgroup per possible quarter of every item (16) would cost
 // 1 us per 256 of them that have none (32 experts, 280 rows, K = 768 and 512:
-// both phases 50 us, so 35).  (us of phase 1 and 2 in whole units, in quarters:
+// both phases 50 us, so 31).  (us of phase 1 and 2 in whole units, in quarters:
 // 8 experts of 128 rows, K = 2048 and 1408, 176 and 128 quarters, 43 and 33, 33
 // and 25; 2048 ragged rows, K = 1024 and 1408, 440 and 160 quarters, 31 and 39,
 // 38 and 25.)  The workgroup's item comes out of the counting lanes' registers:
