@@ -660,7 +660,9 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
     // 483 and 448, [448] 88 and 67, [1040] 1048 and 951 (a workgroup per item),
     // but [352] 770 and 824, [376] 117 and 129; 32 experts [352] of 16, 256, 512
     // and 1024 rows each, K = 2048, 98 and 110, 139 and 144, 231 and 209, 448 and
-    // 383.  Phase 2's units are shorter and store twice the chunks: [176] 44 and
+    // 383.  (Units in turn stay on their item's XCD, so one expert with most of
+    // the rows and one column tile fills one XCD only: 4 experts, 28140 Zipf(1)
+    // rows, K = 256, 128 columns, [216], 42 against 29 in whole items.)  Phase 2's units are shorter and store twice the chunks: [176] 44 and
     // 48, [312] 214 and 220, [448] 254 and 233, [512] 390 and 417, [720] 349 and
     // 254, [1520] 515 and 497.
     const int few = phase == 1 ? kScan : 512;
