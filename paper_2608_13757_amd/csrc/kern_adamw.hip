@@ -73,11 +73,17 @@ __global__ void __launch_bounds__(64 * 6) adamw_kernel(AdamParams P) {
   const uint32_t CH = (uint32_t)P.ch, W = (uint32_t)P.wn;
   const int64_t n_chunks = (P.n + CH - 1) / CH;
   const uint32_t blocks = CH / 256u;      // 1 KiB blocks per array and chunk
+  // Not unrolled: a chunk has one to four blocks, and the compiler's copies for
+  // eight and more, for each array and place of call, made the loop around them
+  // slower although never run (us unrolled and not: 2^20 parameters, launch after
+  // launch, 9.3 and 9.0; 2^23 in chunks of 256, a ring of two slots, 1, 2 and 4
+  // vector waves 43.2 and 40.5, 47.4 and 42.4, 78.1 and 47.1).
   auto load_chunk = [&](int64_t chunk, unsigned char *dst) {
     const int64_t e0 = chunk * (int64_t)CH;     // first parameter of the chunk
     const float *src[4] = {P.p, P.g, P.m, P.v};
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
+#pragma unroll 1
       for (uint32_t b = 0; b < blocks; ++b) {
         // lanes past N load the last 4 floats instead (never stored), so
         // that every step issues exactly per_step loads: the counted
@@ -92,9 +98,9 @@ __global__ void __launch_bounds__(64 * 6) adamw_kernel(AdamParams P) {
   // A launch of one or two chunks per workgroup is a chain of latencies (trip
   // offset, trip, chunk, stores): barrier-free, the first chunk (its slot is
   // free) is loaded before the trip is known and the counters are cleared.  (us
-  // without and with: 2^18 parameters, a chunk per workgroup, 7.6 and 7.3; 2^20,
-  // two chunks, 9.4 and 9.3; 3 * 2^20 17.2 and 16.5, 2^22 22.6 and 21.9; with the
-  // caches full of other data 2^20 19.4 and 18.1.)
+  // without and with: 2^18 parameters, a chunk per workgroup, 7.4 and 7.0; 2^20,
+  // two chunks, 9.3 and 9.0; 3 * 2^20 16.5 and 16.0, 2^22 21.7 and 21.3; with the
+  // caches full of other data 2^18 10.1 and 9.7, 2^20 12.4 and 12.1.)
   constexpr bool kAhead = kMode != BFS_MODE_BARRIER && !kInstr;
   const bool ahead = kAhead && c0 >= 0 && c0 < n_chunks;
   if (ahead && wave == 0) load_chunk(c0, ring);
@@ -302,9 +308,10 @@ bfs_status launch_adamw(const bfs_plan *p, DevImage *img, const void *const *buf
   // Plain stores where p, g, m and v fit the 256 MiB last-level cache but not,
   // by some margin, the L2s (32 MiB): the next launch on them finds the results
   // there.  Beyond, they push out what that launch reads.  (us with nontemporal
-  // and with plain stores: 2.07 M parameters 10.6 and 11.1, 2.2 M 12.9 and 13.2;
-  // 3.1 M 16.5 and 16.1, 4.2 M 21.9 and 21.0, 8.4 M 41.4 and 39.4; 20 M 89.6 and
-  // 91.3, 33.8 M 186 and 204.  With the caches full of other data alike.)
+  // and with plain stores: 2.07 M parameters 10.7 and 11.1, 2.2 M 12.8 and 13.0;
+  // 3.1 M 16.9 and 16.0, 4.2 M 21.5 and 21.3, 8.4 M 40.2 and 38.7; 20 M 88.3 and
+  // 89.9, 33.8 M 197 and 199.  With the caches full of other data 2.2 M 17.0 and
+  // 17.6, 3.1 M 21.7 and 21.3, 8.4 M 50.0 and 47.1, but 20 M 139 and 132.)
   return N * 16 > kPlainFrom && N * 16 <= kPlainTo ? go(adamw_kernel<BFS_MODE_BARRIER_FREE, false, true>)
                                                   : go(adamw_kernel<BFS_MODE_BARRIER_FREE, false, false>);
 }
