@@ -547,9 +547,11 @@ __global__ void __launch_bounds__(768) moe_many_kernel(MoeParams P, Split D) {
 // both phases 50 us, so 31).  (us of phase 1 and 2 in whole units, in quarters:
 // 8 experts of 128 rows, K = 2048 and 1408, 176 and 128 quarters, 43 and 33, 33
 // and 25; 2048 ragged rows, K = 1024 and 1408, 440 and 160 quarters, 31 and 39,
-// 38 and 25.)  The workgroup's item comes out of the counting lanes' registers:
-// read from memory again it cost 1.5 us (128 items of a few rows, K = 256: 12.7
-// us, so 11.2; whole items without a count 9.8).
+// 38 and 25.)  The workgroup's item comes out of LDS, where every wave keeps what
+// it counts: read from memory again it cost 1.5 us (128 items of a few rows, K =
+// 256: 12.7 us, so 11.2; whole items without a count 9.8), and kept in the lanes'
+// registers these went to scratch memory (2048 rows, K = 1024 and 1408, both phases:
+// 56.5 us from memory, 55.9 from the lanes, so 55.5).
 constexpr int kScan = 128, kCUs = 256;
 
 template <int kPhase, int kPM>
@@ -575,6 +577,23 @@ __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
       trip[h] = (uint32_t)P.trips[at[h]];
     }
   }
+  // The items in the ring's memory, which no load fills before every wave has
+  // reached the barrier in run_units, its item read.  (Every wave writes all of
+  // them, the same values, so that none waits for another.)
+  const uint32_t table = lds_addr(lds) + kCntBytes;
+  static_assert(32 * kScan <= 2 * Unit<128, 128>::kSlot, "the items fit the smallest ring");
+#pragma unroll
+  for (int h = 0; h < kScan / 64; ++h) {
+    const uint32_t row = table + 32u * (64u * h + lane_id());
+    *(BFS_LDS u32x4 *)(uintptr_t)row = u32x4{(uint32_t)e[h], (uint32_t)n0[h], (uint32_t)mt0[h], (uint32_t)lo[h]};
+    *(BFS_LDS u32x4 *)(uintptr_t)(row + 16u) = u32x4{(uint32_t)(hi[h] - lo[h]), trip[h], 0u, 0u};
+  }
+  auto item_of = [&](int w) __attribute__((always_inline)) {
+    const uint32_t row = table + 32u * (uint32_t)w;
+    const u32x4 a = *(const BFS_LDS u32x4 *)(uintptr_t)row, b = *(const BFS_LDS u32x4 *)(uintptr_t)(row + 16u);
+    return Item{(int32_t)uniform(a.x), (int32_t)uniform(a.y), (int32_t)uniform(a.z), (int32_t)uniform(a.w),
+                (int32_t)uniform(b.x), uniform(b.y)};
+  };
   // quarters up to and with items lane and 64 + lane (an item without rows but
   // with a trip has two, so that the trip is checked as any other's)
   uint32_t own[kScan / 64], upto[kScan / 64], quarters = 0;
@@ -599,7 +618,6 @@ __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
     if (blockIdx.x / 8u >= per || q >= quarters) return;
     int wg = 0;
     uint32_t sub = 0, parts = 2;
-    Item I{};
 #pragma unroll
     for (int h = kScan / 64 - 1; h >= 0; --h) {
       const uint64_t above = __ballot(upto[h] > q);
@@ -608,18 +626,16 @@ __global__ void __launch_bounds__(768) moe_small_kernel(MoeParams P, Split D) {
         wg = 64 * h + at;
         parts = uniform(__shfl(own[h], at));
         sub = q - (uniform(__shfl(upto[h], at)) - parts);
-        auto of = [&](int32_t v) { return __builtin_amdgcn_readlane(v, at); };
-        I = Item{of(e[h]), of(n0[h]), of(mt0[h]), of(lo[h]), of(hi[h]) - of(lo[h]), (uint32_t)of((int32_t)trip[h])};
       }
     }
     Split Q = D;
     Q.sm = (int32_t)(parts / 2u);
     Q.sn = 2;
-    run_units<kPhase, 128, 128>(P, Q, lds, wg, (int)sub, I);
+    run_units<kPhase, 128, 128>(P, Q, lds, wg, (int)sub, item_of(wg));
     return;
   }
   const int wg = blockIdx.x % D.items, sub = blockIdx.x / D.items;
-  if (wg < D.n_wg && sub < D.sm) run_units<kPhase, kPM, 256>(P, D, lds, wg, sub, read_item(P, wg));
+  if (wg < D.n_wg && sub < D.sm) run_units<kPhase, kPM, 256>(P, D, lds, wg, sub, item_of(wg));
 }
 
 }  // namespace
@@ -662,9 +678,10 @@ bool bfsmoe::launch_parts(const MoeParams &P, int phase, int bm, bool linear, in
     // and 1024 rows each, K = 2048, 98 and 110, 139 and 144, 231 and 209, 448 and
     // 383.  (Units in turn stay on their item's XCD, so one expert with most of
     // the rows and one column tile fills one XCD only: 4 experts, 28140 Zipf(1)
-    // rows, K = 256, 128 columns, [216], 42 against 29 in whole items.)  Phase 2's units are shorter and store twice the chunks: [176] 44 and
-    // 48, [312] 214 and 220, [448] 254 and 233, [512] 390 and 417, [720] 349 and
-    // 254, [1520] 515 and 497.
+    // rows, K = 256, 128 columns, [216], 42 against 29 in whole items.)  Phase 2's
+    // units are shorter and store twice the chunks: [176] 44 and 48, [312] 214 and
+    // 220, [448] 254 and 233, [512] 390 and 417, [720] 349 and 254, [1520] 515 and
+    // 497.
     const int few = phase == 1 ? kScan : 512;
     const int items = (n_wg + 7) / 8 * 8;
     const size_t table = (size_t)items / 8 * 32;
